@@ -64,7 +64,9 @@ enum {
 /* Flags of xeng_plan / xeng_plan_batch. */
 enum {
     XENG_FORM_I8 = 0,        /* int8 MFMA, int32 accumulators (default) */
-    XENG_FORM_F8 = 1,        /* FP8 e4m3 MFMA, f32 accumulators flushed to int32 */
+    XENG_FORM_F8 = 1,        /* FP8 e4m3 MFMA, f32 accumulators flushed to int32; both forms
+                                are exact, and both take the packed path (FP6) where
+                                xeng_correlate chooses it */
     XENG_FORM_MASK = 0xff,
     XENG_ACCUMULATE = 1 << 8, /* add into vis instead of overwriting it */
     XENG_SHARED_VIS = 1 << 9  /* batch plans only, with XENG_ACCUMULATE: instances may share
@@ -110,6 +112,15 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * The channel kernel (see xeng_plan_set_tuning) with S > 1 time slices keeps
  * the slices' partial outputs, S F N(N+1) int32, in plan-owned device memory
  * allocated on first use (grown, after the plan's last call, when S grows).
+ * Frames of more than 640 inputs and enough work take the packed path (unless
+ * the plan names a kernel): the samples are repacked into FP6 operands (the
+ * 4-bit codes are FP6 numbers as they stand) and correlated on FP6 matrix
+ * cores, exactly, in segments of at most XENG_F8_FLUSH_MAX samples.  The
+ * operands (1.5 bytes a sample of one segment) and the partial outputs of
+ * sliced tiles are plan-owned device memory, allocated on first use: at most 4
+ * GiB of operands (or one channel's), larger frames run in groups of channels.
+ * A call under HIP graph capture, or one for which that memory cannot be
+ * allocated, takes the tile kernels.
  * Errors: XENG_EINVAL (NULL plan or pointer, T < 1), XENG_EPLAN (N or F differ
  * from the plan, T > T_max), XENG_EOVERFLOW (T > XENG_T_EXACT_MAX),
  * XENG_ENOMEM (that memory cannot be allocated), XENG_EHIP.
@@ -137,9 +148,10 @@ int xeng_correlate(xeng_plan_t p, const uint8_t *samples, int N, int F, int T,
  *            time slices store partial outputs that a second kernel sums
  *            into vis (int8 form only; the FP8 form, time shifting through
  *            the loads and N > 256 use 1).  Automatic: 5 for the int8 form at 128 < N <= 256 with
- *            N % 16 == 0 and 16-byte-aligned samples, else 1, the fastest on
- *            gfx950 at the measured sizes; the autotuner (tune.tune_plain)
- *            picks per shape.
+ *            N % 16 == 0 and 16-byte-aligned samples, the packed path (see
+ *            xeng_correlate) on large frames of more than 640 inputs, else 1,
+ *            the fastest on gfx950 at the measured sizes; the autotuner
+ *            (tune.tune_plain) picks per shape.
  * Errors: XENG_EINVAL (NULL plan, negative split_t, kernel outside 0..5).
  */
 int xeng_plan_set_tuning(xeng_plan_t p, int split_t, int kernel);

@@ -19,7 +19,7 @@ LIB = os.path.join(PKG, "libxeng.so")
 CEILING = os.path.join(PKG, "mfma_ceiling")
 SOURCES = ("xcorr_plain.hip", "xcorr_chan.hip", "xcorr_gated.hip", "xcorr_batch.hip",
            "xcorr_wide.hip", "xeng_flags.hip", "xeng_beam.hip", "xeng_shift.hip",
-           "xeng_noalloc.hip", "xeng_api.cpp")
+           "xeng_noalloc.hip", "xeng_pack.hip", "xcorr_packed.hip", "xeng_api.cpp")
 OBJDIR = os.path.join(PKG, "_build")
 ARCH = "gfx950"
 

@@ -17,6 +17,7 @@
 #include "xeng_chan.hpp"
 #include "xeng_internal.hpp"
 #include "xeng_noalloc.hpp"
+#include "xeng_packed.hpp"
 
 namespace {
 
@@ -27,6 +28,10 @@ constexpr int kChanMax = 2 * kTile;  // inputs of the channel kernel
 // Output gating: extra work gates one launch segment can need when gates are
 // split (fewer than 2 x 64 = 128; see xeng_correlate_gated).
 constexpr int kSplitMax = 128;
+// Packed path: device memory of a plan's operands, at most (a channel that
+// takes more on its own gets what it needs); larger frames run in groups of
+// channels.
+constexpr size_t kPackedMax = 4ull << 30;
 constexpr int kStageRing = 4;  // pinned staging copies of a batch plan's instance table
 
 enum PlanKind { PLAN_SINGLE = 1, PLAN_BATCH = 2 };
@@ -40,7 +45,7 @@ struct xeng_plan_s {
   int form = XENG_FORM_I8;
   bool accumulate = false;
   int split_t = 0;  // 0 = automatic
-  int kernel = 0;   // 0 = automatic, 1 = 128 x 128 tiles, 2 = 128 x 256 tiles,
+  int kernel = 0;   // 0 = automatic (packed path included), 1 = 128 x 128 tiles, 2 = 128 x 256 tiles,
                     // 3 / 4 = 128 x 128 tiles with split / common diagonal roles
   int cu_count = 0;
   std::string err;
@@ -84,6 +89,14 @@ struct xeng_plan_s {
   size_t chan_ws_ints = 0;
   hipEvent_t chan_ws_used = nullptr;
   bool chan_ws_pending = false;
+
+  // packed path: operands and code sums of a segment of a channel group
+  // (plan-owned, allocated on first use) and the event of the last call that
+  // read them
+  uint8_t* d_packed = nullptr;
+  size_t packed_bytes = 0;
+  hipEvent_t packed_used = nullptr;
+  bool packed_pending = false;
 
   // time shifting (xeng_plan_set_delays): per-segment delays and block maxima
   bool shift = false;
@@ -407,6 +420,214 @@ static int chan_workspace(xeng_plan_t p, size_t ints, hipStream_t s) {
   return XENG_OK;
 }
 
+// The packed path (xeng_packed.hpp): bytes of one channel's operands and code
+// sums (at most) over `len` samples.
+static size_t packed_channel_bytes(int N, int len) {
+  const size_t steps = 4 * (size_t)((len + xeng::PK_GRAIN - 1) / xeng::PK_GRAIN);
+  const size_t blocks = (N + kTile - 1) / kTile;
+  const size_t nsum = (steps * xeng::PK_STEP + xeng::PK_SUMB_SHORT - 1) / xeng::PK_SUMB_SHORT;
+  return steps * blocks * xeng::BLOCK_BYTES + nsum * blocks * kTile * sizeof(int2);
+}
+
+// The packed path's schedule for W tiles of `plen` samples on `cus` compute
+// units (one workgroup each): uniform slices, or R full rounds of whole tiles
+// and the rest in slices that fill one more round.
+struct PackedSchedule {
+  int nslices, slice_len;
+  long long head;
+  int tail_slices, tail_len;
+};
+
+static PackedSchedule packed_schedule(long long W, int plen, int sumb, int cus, int split_t) {
+  auto round_slice = [&](int n) {
+    const int l = (plen + n - 1) / n;
+    return (l + sumb - 1) / sumb * sumb;
+  };
+  PackedSchedule c{1, plen, W, 0, 0};
+  if (split_t > 0) {
+    c.slice_len = round_slice(split_t);
+    c.nslices = (plen + c.slice_len - 1) / c.slice_len;
+    return c;
+  }
+  // microseconds: a step of a tile, the start and end of a round, and what a
+  // sliced item adds (its partial blocks written and read back)
+  const double step = 0.42, round = 12.0, fixed = 10.0, item = 0.10;
+  const double steps = plen / (double)xeng::PK_STEP;
+  auto rounds = [&](long long n) { return (double)((n + cus - 1) / cus); };
+  double best = rounds(W) * (steps * step + round);
+  const int smax = std::min(16, plen / sumb);
+  for (int S = 2; S <= smax; ++S) {
+    const int sl = round_slice(S), n = (plen + sl - 1) / sl;
+    if (n != S) continue;
+    const double t = rounds(W * n) * (sl / (double)xeng::PK_STEP * step + round) + fixed + item * W * n;
+    if (t < best) {
+      best = t;
+      c.nslices = n;
+      c.slice_len = sl;
+    }
+  }
+  const long long R = W / cus, rem = W - R * cus;
+  if (R > 0 && rem > 0) {
+    for (int S = 2; S <= smax; ++S) {
+      const int sl = round_slice(S), n = (plen + sl - 1) / sl;
+      if (n != S) continue;
+      const double t = R * (steps * step + round) +
+                       rounds(rem * n) * (sl / (double)xeng::PK_STEP * step + round) + fixed +
+                       item * rem * n;
+      if (t < best) {
+        best = t;
+        c.nslices = 1;
+        c.slice_len = plen;
+        c.head = R * cus;
+        c.tail_slices = n;
+        c.tail_len = sl;
+      }
+    }
+  }
+  return c;
+}
+
+// When the packed path is chosen (tuning kernel 0).  Packing moves 2.5 bytes of
+// HBM traffic a sample (0.52 ms for a GiB of samples) and the FP6 correlation
+// runs at about 1.8 times the rate of the int8 tiles, so it pays from about
+// 700 inputs; measured on frames of 512..2048 inputs, 1..64 channels and
+// 512..32768 samples (microseconds, tile kernels / packed path):
+//   N = 2048, F = 16, T = 32768  3275 / 2372    N = 768, F = 16, T = 32768  522 / 524
+//   N = 1024, F = 16, T = 32768   862 / 718     N = 512, F = 16, T = 32768  258 / 281
+// It takes three launches and at least 32 us, which small frames do not: below
+// 230,000 tile-samples (128 x 128 tiles x samples) the tile kernels win
+//   N = 1024, F = 1, T = 8192 (295,000)  63 / 49    T = 2048 (74,000)    30 / 40
+//   N = 768,  F = 1, T = 32768 (688,000) 79 / 71    T = 8192 (172,000)   45 / 50
+// and short integrations are bound by the visibilities, not the products:
+//   N = 2048, F = 16, T = 512  102 / 128    T = 2048  274 / 240
+static bool packed_pays(int N, int F, int T) {
+  return N > 640 && T >= 1536 && tiles_per_channel(N) * F * (long long)T >= 230000;
+}
+
+// Whether `s` is being captured into a HIP graph (or cannot be asked): such a
+// call takes the kernels that need no plan-owned workspace, which a later call
+// could replace or overwrite between the graph's replays.
+static bool stream_captures(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+static int packed_sumb(int blocks, int nchan, int plen, int cus) {
+  const long long wgs = (long long)blocks * nchan *
+                        ((plen + xeng::PK_SUMB_LONG - 1) / xeng::PK_SUMB_LONG);
+  return wgs >= 4LL * cus ? xeng::PK_SUMB_LONG : xeng::PK_SUMB_SHORT;
+}
+
+// Correlate by the packed path: per segment of at most XENG_F8_FLUSH_MAX
+// samples and group of channels that fits the workspace, pack the samples and
+// correlate the packed operands.
+static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
+                            int32_t* vis, hipStream_t s) {
+  const int blocks = (N + kTile - 1) / kTile, tpc = xeng::packed_tiles(blocks);
+  const int seg = XENG_F8_FLUSH_MAX, seg_len = std::min(T, seg);
+  const size_t per_chan = packed_channel_bytes(N, seg_len);
+  const int group = (int)std::max<size_t>(1, std::min<size_t>(F, kPackedMax / per_chan));
+  // partial blocks: the largest schedule of the call
+  size_t part = 0;
+  for (int k = 0; k < 4; ++k) {
+    const int len = k & 1 ? T % seg : seg_len, nch = k & 2 ? F % group : group;
+    if (len == 0 || nch == 0) continue;
+    const int plen = (len + xeng::PK_GRAIN - 1) / xeng::PK_GRAIN * xeng::PK_GRAIN;
+    const PackedSchedule c =
+        packed_schedule((long long)tpc * nch, plen, packed_sumb(blocks, nch, plen, p->cu_count),
+                        p->cu_count, p->split_t);
+    const long long items = c.nslices > 1 ? c.head * c.nslices
+                                          : ((long long)tpc * nch - c.head) * c.tail_slices;
+    part = std::max(part, (size_t)items * xeng::PK_PART * sizeof(int2));
+  }
+  hipError_t e = hipSuccess;
+  const size_t operands = (per_chan * group + 255) / 256 * 256, need = operands + part;
+  if (!p->packed_used) {
+    e = hipEventCreateWithFlags(&p->packed_used, hipEventDisableTiming);
+    if (e != hipSuccess) return hip_fail(p, e, "hipEventCreate");
+  }
+  if (need > p->packed_bytes) {
+    if (p->packed_pending) {
+      e = hipEventSynchronize(p->packed_used);
+      if (e != hipSuccess) return hip_fail(p, e, "hipEventSynchronize");
+      p->packed_pending = false;
+    }
+    if (p->d_packed) (void)hipFree(p->d_packed);
+    p->d_packed = nullptr;
+    p->packed_bytes = 0;
+    e = hipMalloc((void**)&p->d_packed, need);
+    if (e != hipSuccess) {
+      p->d_packed = nullptr;
+      (void)hipGetLastError();
+      if (e == hipErrorOutOfMemory) return XENG_ENOMEM;
+      return hip_fail(p, e, "hipMalloc (packed operands)");
+    }
+    p->packed_bytes = need;
+  } else if (p->packed_pending) {
+    e = hipStreamWaitEvent(s, p->packed_used, 0);
+    if (e != hipSuccess) return hip_fail(p, e, "hipStreamWaitEvent");
+  }
+  const long long row = (long long)F * N, NB2 = (long long)N * (N + 1);
+  const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0);
+  for (int t0 = 0; t0 < T; t0 += seg) {
+    const int len = std::min(seg, T - t0);
+    const bool add = p->accumulate || t0 > 0;
+    for (int f0 = 0; f0 < F; f0 += group) {
+      const int nch = std::min(group, F - f0);
+      xeng::PackArgs k;
+      k.samples = samples + (long long)f0 * N;
+      k.frame_end = samples + (long long)T * row;
+      k.N = N;
+      k.nchan = nch;
+      k.t0 = t0;
+      k.t1 = t0 + len;
+      k.row_stride = row;
+      k.blocks = blocks;
+      k.steps = 4 * ((len + xeng::PK_GRAIN - 1) / xeng::PK_GRAIN);
+      const int plen = k.steps * xeng::PK_STEP;
+      k.sumb = packed_sumb(blocks, nch, plen, p->cu_count);
+      k.nsum = (plen + k.sumb - 1) / k.sumb;
+      k.packed = p->d_packed;
+      k.sums = reinterpret_cast<int2*>(p->d_packed +
+                                       (size_t)nch * k.steps * blocks * xeng::BLOCK_BYTES);
+      k.seg_delay = p->shift ? p->d_seg_delay : nullptr;
+      e = xeng::launch_pack(k, aligned, s);
+      if (e != hipSuccess) return hip_fail(p, e, "pack launch");
+
+      const PackedSchedule c =
+          packed_schedule((long long)tpc * nch, plen, k.sumb, p->cu_count, p->split_t);
+      xeng::PackedArgs a;
+      a.packed = k.packed;
+      a.sums = k.sums;
+      a.vis = vis + f0 * NB2;
+      a.partial = part ? reinterpret_cast<int2*>(p->d_packed + operands) : nullptr;
+      a.N = N;
+      a.nchan = nch;
+      a.steps = k.steps;
+      a.blocks = blocks;
+      a.nsum = k.nsum;
+      a.sumb = k.sumb;
+      a.tiles_per_chan = tpc;
+      a.nslices = c.nslices;
+      a.slice_len = c.slice_len;
+      a.write_mode = add ? xeng::WM_ADD : xeng::WM_STORE;
+      a.head_tiles = (int)c.head;
+      a.tail_slices = c.tail_slices;
+      a.tail_len = c.tail_len;
+      e = xeng::launch_packed(a, s);
+      if (e != hipSuccess) return hip_fail(p, e, "packed correlation launch");
+    }
+  }
+  e = hipEventRecord(p->packed_used, s);
+  if (e != hipSuccess) return hip_fail(p, e, "hipEventRecord");
+  p->packed_pending = true;
+  return p->shift ? mark_tables(p, s) : XENG_OK;
+}
+
 int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, int32_t* vis,
                    void* stream) {
   if (!p || !samples || !vis || N < 1 || F < 1 || T < 1) return XENG_EINVAL;
@@ -416,6 +637,11 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   int rc = ensure_cu_count(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (p->kernel == 0 && packed_pays(N, F, T) && !stream_captures(s)) {
+    rc = correlate_packed(p, samples, N, F, T, vis, s);
+    if (rc != XENG_ENOMEM) return rc;
+    // no room for the operands: the tile kernels need none
+  }
   // delays: in the loads, or by a shifted copy of the frame
   const bool kshift = p->shift && !p->shift_copy;
   if (p->shift && p->shift_copy) {
@@ -1233,6 +1459,8 @@ int xeng_destroy(xeng_plan_t p) {
   if (p->d_shifted) (void)hipFree(p->d_shifted);
   if (p->d_chan_ws) (void)hipFree(p->d_chan_ws);
   if (p->chan_ws_used) (void)hipEventDestroy(p->chan_ws_used);
+  if (p->d_packed) (void)hipFree(p->d_packed);
+  if (p->packed_used) (void)hipEventDestroy(p->packed_used);
   if (p->d_fU) (void)hipFree(p->d_fU);
   if (p->d_fX) (void)hipFree(p->d_fX);
   if (p->d_fint) (void)hipFree(p->d_fint);

@@ -102,8 +102,8 @@ class Plan:
         return self._h.value
 
     def set_tuning(self, split_t: int = 0, kernel: int = 0) -> None:
-        """split_t: time slices per tile (0 = automatic); kernel: 0 automatic,
-        1 = 128 x 128 tiles, 2 = 128 x 256 tiles (needs N % 16 == 0), 3 / 4 =
+        """split_t: time slices per tile (0 = automatic); kernel: 0 automatic
+        (above 640 inputs, large frames are repacked into FP6 operands), 1 = 128 x 128 tiles, 2 = 128 x 256 tiles (needs N % 16 == 0), 3 / 4 =
         128 x 128 tiles with split / common wave roles in diagonal tiles, 5 =
         the channel kernel (one workgroup per channel and time slice; int8,
         N <= 256; other plans use 1)."""
@@ -276,6 +276,12 @@ def correlate(samples: torch.Tensor, form: str = "i8", vis: Optional[torch.Tenso
               stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """One-shot correlation of a frame (plans, runs and frees a plan)."""
     T, F, N = _check_samples(samples)
+    # Above 640 inputs a plan may keep repacked operands, whose allocation and
+    # release take about 0.3 ms: a plan used once gains that back only on
+    # frames of some 4e11 complex MACs (2729 us against 3293 us on 1.1e12;
+    # 428 us against 202 us on 1.7e10)
+    if kernel == 0 and N > 640 and F * T * num_baselines(N) < 5e11:
+        kernel = 1
     with Plan(N, F, T, form=form, accumulate=accumulate, split_t=split_t, kernel=kernel) as p:
         return p.correlate(samples, vis, stream)
 
