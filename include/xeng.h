@@ -213,7 +213,9 @@ int xeng_correlate_gated(xeng_plan_t p, const uint8_t *samples, int N, int F, in
  * applied in the correlation's loads at almost no cost; delays that differ
  * inside a block make each call first copy the frame, shifted, into a
  * plan-owned buffer of T_max F N bytes (allocated here, once), which the
- * correlation then reads unshifted.
+ * correlation then reads unshifted; calls on the packed path (see
+ * xeng_correlate; with such delays from 128 inputs on) apply them while
+ * repacking instead.
  * Errors: XENG_EINVAL (NULL plan, a delay outside 0..D_max, delays that differ
  * within a 16-input group, D_max too large), XENG_EPLAN (batch plan),
  * XENG_ENOMEM, XENG_EHIP.

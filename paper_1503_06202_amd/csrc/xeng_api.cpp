@@ -104,6 +104,7 @@ struct xeng_plan_s {
   int* d_blk_delay = nullptr;
   // delays that differ inside a 128-input block: shifted copy of the frame
   bool shift_copy = false;
+  int shift_max = 0;  // the largest delay
   uint8_t* d_shifted = nullptr;
 
   // flagged data (xeng_plan_flagged): event frame, its correlation and counters
@@ -375,6 +376,7 @@ int xeng_plan_set_delays(xeng_plan_t p, const int32_t* delays, int D_max) {
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? XENG_ENOMEM : hip_fail(p, e, "delay upload");
   p->shift = true;
   p->shift_copy = fine;
+  p->shift_max = *std::max_element(seg.begin(), seg.end());
   return XENG_OK;
 }
 
@@ -500,8 +502,16 @@ static PackedSchedule packed_schedule(long long W, int plen, int sumb, int cus, 
 //   N = 768,  F = 1, T = 32768 (688,000) 79 / 71    T = 8192 (172,000)   45 / 50
 // and short integrations are bound by the visibilities, not the products:
 //   N = 2048, F = 16, T = 512  102 / 128    T = 2048  274 / 240
-static bool packed_pays(int N, int F, int T) {
-  return N > 640 && T >= 1536 && tiles_per_channel(N) * F * (long long)T >= 230000;
+// Delays that differ inside a block of 128 inputs (shift_copy) cost the tile
+// kernels a copy of the frame that fetches every line eight times (1.39 ms a
+// GiB), and the packed path only a longer packing pass (0.93 ms): there it
+// pays from 128 inputs on,
+//   N = 128, F = 16, T = 32768  131 / 110    N = 384, F = 64, T = 4096   259 / 130
+//   N = 512, F = 4,  T = 8192 (328,000)  80 / 64    N = 512, F = 1, T = 32768 (328,000)  76 / 81
+static bool packed_pays(int N, int F, int T, bool shift_copy) {
+  const long long work = tiles_per_channel(N) * F * (long long)T;
+  if (T < 1536) return false;
+  return shift_copy ? N >= 128 && work >= 340000 : N > 640 && work >= 230000;
 }
 
 // Whether `s` is being captured into a HIP graph (or cannot be asked): such a
@@ -594,7 +604,10 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
       k.packed = p->d_packed;
       k.sums = reinterpret_cast<int2*>(p->d_packed +
                                        (size_t)nch * k.steps * blocks * xeng::BLOCK_BYTES);
+      // delays that differ inside a block: by source windows
       k.seg_delay = p->shift ? p->d_seg_delay : nullptr;
+      k.dmax = p->shift && p->shift_copy ? p->shift_max : -1;
+      k.win = k.sumb;
       e = xeng::launch_pack(k, aligned, s);
       if (e != hipSuccess) return hip_fail(p, e, "pack launch");
 
@@ -637,7 +650,7 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   int rc = ensure_cu_count(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->kernel == 0 && packed_pays(N, F, T) && !stream_captures(s)) {
+  if (p->kernel == 0 && packed_pays(N, F, T, p->shift && p->shift_copy) && !stream_captures(s)) {
     rc = correlate_packed(p, samples, N, F, T, vis, s);
     if (rc != XENG_ENOMEM) return rc;
     // no room for the operands: the tile kernels need none

@@ -42,6 +42,8 @@ struct PackArgs {
   int steps, blocks;       // steps per channel, blocks of 128 inputs
   int nsum, sumb;          // sum blocks per channel, and samples of one
   const int* seg_delay;    // delays per 16 inputs, or NULL
+  int dmax;                // the largest delay, to pack by source windows; or -1
+  int win;                 // source rows per window, a multiple of 64
 };
 
 // Tiles of a channel: per macro row I (256 inputs), its diagonal triangle, then

@@ -130,6 +130,24 @@ def test_packed_delays(N, step):
     assert np.array_equal(got.cpu().numpy(), oracle.to_int32(oracle.correlate_shifted(ext, D, d)))
 
 
+# delays per 16 inputs take the packed path from 128 inputs on (340,000
+# tile-samples); windows of the source meet the steps at every offset
+@pytest.mark.parametrize("N,F,T,D", [(128, 60, 6011, 1), (144, 16, 7200, 31), (200, 16, 7111, 33),
+                                     (300, 4, 14400, 2500), (656, 1, 33000, 20000)])
+def test_packed_group_delays(N, F, T, D):
+    ext = rand_frame(N + D, D + T, F, N)
+    r = np.random.default_rng(N)
+    d = np.repeat(r.integers(0, D + 1, (N + 15) // 16), 16)[:N].astype(np.int32)
+    d[:16], d[16:32] = 0, D
+    dev = torch.from_numpy(ext).to(DEV)
+    ref = oracle.to_int32(oracle.correlate_shifted(ext, D, d))
+    with Plan(N, F, T) as p:
+        p.set_delays(d, D)
+        assert np.array_equal(p.correlate(dev[D:]).cpu().numpy(), ref)
+        p.set_delays(None)  # off again, on the same workspace
+        assert np.array_equal(p.correlate(dev[D:].contiguous()).cpu().numpy(), want(ext[D:]))
+
+
 def test_packed_workspace_orders_streams_and_grows():
     N = 700
     a, b, c = (rand_frame(40 + k, T, 2, N) for k, T in enumerate((5504, 5504, 9000)))
