@@ -140,15 +140,15 @@ int xeng_correlate(xeng_plan_t p, const uint8_t *samples, int N, int F, int T,
  *            3 / 4 = 128 x 128 with the wave roles of diagonal tiles fixed:
  *            3 splits the sub-tile above the diagonal between two waves and
  *            skips the block below it, 4 keeps the off-diagonal roles (4
- *            applies to 16-byte-aligned frames without time shifting; others
+ *            applies to frames with F N <= 2^25 and no time shifting; others
  *            always split).  1 chooses the diagonal roles by N (split up to
  *            1024 inputs).  5 = the channel kernel: one workgroup of eight
  *            waves per (channel, time slice) covers the whole triangle of a
  *            channel of at most 256 inputs, each sample read once; several
  *            time slices store partial outputs that a second kernel sums
  *            into vis (int8 form only; the FP8 form, time shifting through
- *            the loads and N > 256 use 1).  Automatic: 5 for the int8 form at 128 < N <= 256 with
- *            N % 16 == 0 and 16-byte-aligned samples, the packed path (see
+ *            the loads and N > 256 use 1).  Automatic: 5 for the int8 form at
+ *            128 < N <= 256 (F N <= 2^25), the packed path (see
  *            xeng_correlate) on large frames of more than 640 inputs, else 1,
  *            the fastest on gfx950 at the measured sizes; the autotuner
  *            (tune.tune_plain) picks per shape.

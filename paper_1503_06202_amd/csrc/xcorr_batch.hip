@@ -28,14 +28,14 @@ __global__ void __launch_bounds__(NTHREADS, 2)
     // int8 prefetches two chunks ahead on the fast path (as the plain kernel
     // does); FP8 one
     // (64-bit atomic adds for the tiles of time-sliced instances)
-    if (in.aligned)
+    if (in.fast)
       tile_body<FORM, true, FORM == FORM_I8, false, OneRange, true, true>(
           in.samples, in.vis, in.N, stride, NB, it.f, it.I, it.J, OneRange{it.t0, it.t1}, it.mode,
-          lds);
+          lds, it.t_fast);
     else
       tile_body<FORM, false, false, false, OneRange, true, true>(
           in.samples, in.vis, in.N, stride, NB, it.f, it.I, it.J, OneRange{it.t0, it.t1}, it.mode,
-          lds);
+          lds, it.t_fast);
   }
 }
 

@@ -69,11 +69,11 @@ struct ChanStage {
   }
 };
 
-// Fast loads: both pieces inside the frame (N % 16 == 0, rows 16-byte
-// aligned, F N <= 2^25 so that the offsets of 64 rows fit 31 bits).  `rows`
-// is the chunk's first row of the channel (uniform).  Inputs at or past N
-// read input 0 instead: their plane columns only reach baselines past N,
-// which are never written.
+// Fast loads: both pieces inside the frame, at any alignment (F N <= 2^25, so
+// that the offsets of 64 rows fit 31 bits).  `rows` is the chunk's first row
+// of the channel (uniform).  Pieces at or past N read input 0 instead, and a
+// ragged last piece reads on past input N: those plane columns only reach
+// baselines past N, which are never written.
 __device__ __forceinline__ void chan_load_fast(v4i (&raw)[2], const uint8_t* rows, uint32_t off0,
                                                uint32_t off1) {
   const __amdgpu_buffer_rsrc_t rs =
@@ -82,13 +82,15 @@ __device__ __forceinline__ void chan_load_fast(v4i (&raw)[2], const uint8_t* row
   raw[1] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off1, 0, 0));
 }
 
-// General loads (frame edges, ragged tails, unaligned frames): absent samples
-// and inputs read as the code of 0 + 0i.
+// General loads (frame edges, ragged tails; see load_piece_edge).
 __device__ __forceinline__ void chan_load_edge(v4i (&raw)[2], const uint8_t* samples,
                                                long long row_stride, int f, int N,
-                                               const ChanStage& st, int t_chunk, int t_end) {
-  raw[0] = load_piece_edge(samples, row_stride, f, N, 16 * st.seg, t_chunk + st.row, t_end);
-  raw[1] = load_piece_edge(samples, row_stride, f, N, BT + 16 * st.seg, t_chunk + st.row, t_end);
+                                               const ChanStage& st, int t_chunk, int t_end,
+                                               int t_fast) {
+  raw[0] =
+      load_piece_edge(samples, row_stride, f, N, 16 * st.seg, t_chunk + st.row, t_end, t_fast);
+  raw[1] = load_piece_edge(samples, row_stride, f, N, BT + 16 * st.seg, t_chunk + st.row, t_end,
+                           t_fast);
 }
 
 // Piece k (block k) of a thread: its real (high nibble) and imaginary (low
@@ -402,15 +404,16 @@ __device__ __forceinline__ void chan_step(R& role, ChanCtx& x, const uint8_t* ro
 // chunk c + 1 is stored), then a general loop for the rest.  Loads past the
 // last fast chunk reload it; what they stage is never computed.  Returns the
 // samples integrated, padding of a ragged last chunk included.
-template <bool ALIGNED, class R>
+template <bool FAST, class R>
 __device__ __forceinline__ int chan_range(R& role, ChanCtx& x, const uint8_t* samples,
-                                          long long row_stride, int N, int f, int t_begin,
-                                          int t_end, uint8_t* lds) {
+                                          int t_fast, long long row_stride, int N, int f,
+                                          int t_begin, int t_end, uint8_t* lds) {
   const int len = t_end > t_begin ? t_end - t_begin : 0;
   const int nchunks = (len + KC - 1) / KC;
   const uint8_t* rows = samples + (long long)t_begin * row_stride + (long long)f * N;
   constexpr int B0 = 0, B1 = CH_STAGE;
-  const int nfast = ALIGNED ? len / KC : 0;
+    const int len_fast = FAST ? min(t_end, t_fast) - t_begin : 0;
+  const int nfast = len_fast > 0 ? len_fast / KC : 0;
   const int nsteady = nfast & ~3;
   int c = 0;
   if (nsteady >= 4) {
@@ -433,10 +436,10 @@ __device__ __forceinline__ int chan_range(R& role, ChanCtx& x, const uint8_t* sa
   }
   v4i raw[2];
   auto load = [&](int cc) {
-    if (ALIGNED && (cc + 1) * KC <= len)
+    if (FAST && (cc + 1) * KC <= len_fast)
       chan_load_fast(raw, rows + (long long)cc * KC * row_stride, x.off0, x.off1);
     else
-      chan_load_edge(raw, samples, row_stride, f, N, x.st, t_begin + cc * KC, t_end);
+      chan_load_edge(raw, samples, row_stride, f, N, x.st, t_begin + cc * KC, t_end, t_fast);
   };
   if (c < nchunks) {
     load(c);
@@ -459,7 +462,7 @@ __device__ __forceinline__ int chan_range(R& role, ChanCtx& x, const uint8_t* sa
 }
 
 // The whole work of one wave role: chunks, sums, epilogue.
-template <bool ALIGNED, class R>
+template <bool FAST, class R>
 __device__ __forceinline__ void chan_wave(const ChanArgs& a, int f, int slice, int t_begin,
                                           int t_end, int wave, uint8_t* lds) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -476,7 +479,7 @@ __device__ __forceinline__ void chan_wave(const ChanArgs& a, int f, int slice, i
   *reinterpret_cast<v4i*>(sum_slot(lds)) = v4i{0, 0, 0, 0};
 
   const int teff =
-      chan_range<ALIGNED>(role, x, a.samples, a.row_stride, a.N, f, t_begin, t_end, lds);
+      chan_range<FAST>(role, x, a.samples, fast_rows(a.t_frame, a.N, f, a.F), a.row_stride, a.N, f, t_begin, t_end, lds);
   if (t_end <= t_begin) __syncthreads();  // every slot is cleared before it is read
 
   // per-input sums: lane l of the wave holds input 32 kSumFrag + l % 32 over
@@ -509,7 +512,7 @@ __device__ __forceinline__ void chan_wave(const ChanArgs& a, int f, int slice, i
 
 }  // namespace
 
-template <bool ALIGNED>
+template <bool FAST>
 __global__ void __launch_bounds__(CH_THREADS, 1) xcorr_chan_kernel(ChanArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[CH_LDS];
   const int b = blockIdx.x;
@@ -519,14 +522,14 @@ __global__ void __launch_bounds__(CH_THREADS, 1) xcorr_chan_kernel(ChanArgs a) {
   // uniform per wave: the role dispatch is a scalar branch
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   switch (wave) {
-    case 0: chan_wave<ALIGNED, OffRole<0, 1, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 1: chan_wave<ALIGNED, OffRole<0, 2, 1>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 2: chan_wave<ALIGNED, OffRole<0, 3, 2>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 3: chan_wave<ALIGNED, OffRole<1, 2, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 4: chan_wave<ALIGNED, OffRole<1, 3, 3>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 5: chan_wave<ALIGNED, OffRole<2, 3, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
-    case 6: chan_wave<ALIGNED, DiagRole<0, 3>>(a, f, s, t_begin, t_end, wave, lds); break;
-    default: chan_wave<ALIGNED, DiagRole<2, 1>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 0: chan_wave<FAST, OffRole<0, 1, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 1: chan_wave<FAST, OffRole<0, 2, 1>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 2: chan_wave<FAST, OffRole<0, 3, 2>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 3: chan_wave<FAST, OffRole<1, 2, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 4: chan_wave<FAST, OffRole<1, 3, 3>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 5: chan_wave<FAST, OffRole<2, 3, 0>>(a, f, s, t_begin, t_end, wave, lds); break;
+    case 6: chan_wave<FAST, DiagRole<0, 3>>(a, f, s, t_begin, t_end, wave, lds); break;
+    default: chan_wave<FAST, DiagRole<2, 1>>(a, f, s, t_begin, t_end, wave, lds); break;
   }
 }
 
@@ -568,13 +571,13 @@ hipError_t launch_chan_reduce(const int32_t* partial, int32_t* vis, long long n,
   return hipGetLastError();
 }
 
-hipError_t launch_chan(const ChanArgs& a, bool aligned, hipStream_t stream) {
+hipError_t launch_chan(const ChanArgs& a, bool fast, hipStream_t stream) {
   if (a.N < 1 || a.N > CH_IN || a.nslices < 1 || a.slice_len < 1) return hipErrorInvalidValue;
   const long long grid = (long long)a.F * a.nslices;
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), blk(CH_THREADS);
-  if (aligned)
+  if (fast)
     hipLaunchKernelGGL(xcorr_chan_kernel<true>, g, blk, 0, stream, a);
   else
     hipLaunchKernelGGL(xcorr_chan_kernel<false>, g, blk, 0, stream, a);

@@ -36,7 +36,8 @@ struct StageRole {
   }
 };
 
-// Fast path: the four pieces lie inside the frame.  `rows` points at the
+// Fast path: the four pieces lie inside the frame (at any alignment; pieces
+// past input N read into the next channel or row; rows below t_fast).  `rows` points at the
 // chunk's first row of this channel (uniform across the workgroup); offI /
 // offJ add the thread's first I / J row and its inputs.  Buffer loads: the
 // chunk's base goes into a scalar resource and the row offset of the second
@@ -68,21 +69,31 @@ __device__ __forceinline__ void load_pieces_fast(v4i (&raw)[4], const uint8_t* _
   }
 }
 
-// General path (frame edges, unaligned rows, ragged tails): byte loads of the
-// piece at time t, inputs n_first..n_first+15, delayed by d samples (row
-// t - d, which may lie in the history before the frame); absent samples and
-// inputs read as the code of 0 + 0i.
+// General path (frame edges, ragged tails): the piece at time t, inputs
+// n_first..n_first+15, delayed by d samples (row t - d, which may lie in the
+// history before the frame); absent samples read as the code of 0 + 0i.  One
+// 16-byte load at any alignment (sixteen byte loads, as rows of N % 16 != 0
+// inputs took before, cost 3 to 8 times the frame's whole time: 1927 us against
+// 230 us on N = 250, F = 64, T = 32768): what it reads past input N is the
+// next channel or row, and those inputs' baselines are never written.  Only where
+// the load would pass the frame's end are the bytes read one by one, with
+// absent inputs as the code of 0 + 0i: in row t_fast (the frame's last row, in
+// its last channel, if N is not a multiple of 16; see fast_rows).
 __device__ __forceinline__ v4i load_piece_edge(const uint8_t* __restrict__ samples,
                                                long long row_stride, int f, int N, int n_first,
-                                               int t, int t_end, int d = 0) {
+                                               int t, int t_end, int t_fast, int d = 0) {
   uint32_t w[4] = {0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
-  if (t < t_end) {
+  if (t < t_end && n_first < N) {
     const uint8_t* p = samples + (long long)(t - d) * row_stride + (long long)f * N + n_first;
+    if (t - d < t_fast || n_first + 16 <= N) {
+      __builtin_memcpy(w, p, 16);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      if (n_first + e < N) {
-        const uint32_t sh = 8 * (e & 3);
-        w[e >> 2] = (w[e >> 2] & ~(0xFFu << sh)) | ((uint32_t)p[e] << sh);
+      for (int e = 0; e < 16; ++e) {
+        if (n_first + e < N) {
+          const uint32_t sh = 8 * (e & 3);
+          w[e >> 2] = (w[e >> 2] & ~(0xFFu << sh)) | ((uint32_t)p[e] << sh);
+        }
       }
     }
   }
@@ -95,12 +106,12 @@ template <int NP>
 __device__ __forceinline__ void load_pieces_edge(v4i (&raw)[4], const uint8_t* __restrict__ samples,
                                                  long long row_stride, int f, int N, int nI,
                                                  int nJ, const StageRole& sr, int t_chunk,
-                                                 int t_end, int dI = 0, int dJ = 0) {
-  raw[0] = load_piece_edge(samples, row_stride, f, N, nI, t_chunk + sr.rI, t_end, dI);
-  raw[1] = load_piece_edge(samples, row_stride, f, N, nI, t_chunk + sr.rI + 16, t_end, dI);
+                                                 int t_end, int t_fast, int dI = 0, int dJ = 0) {
+  raw[0] = load_piece_edge(samples, row_stride, f, N, nI, t_chunk + sr.rI, t_end, t_fast, dI);
+  raw[1] = load_piece_edge(samples, row_stride, f, N, nI, t_chunk + sr.rI + 16, t_end, t_fast, dI);
   if (NP == 4) {
-    raw[2] = load_piece_edge(samples, row_stride, f, N, nJ, t_chunk + sr.rJ, t_end, dJ);
-    raw[3] = load_piece_edge(samples, row_stride, f, N, nJ, t_chunk + sr.rJ + 16, t_end, dJ);
+    raw[2] = load_piece_edge(samples, row_stride, f, N, nJ, t_chunk + sr.rJ, t_end, t_fast, dJ);
+    raw[3] = load_piece_edge(samples, row_stride, f, N, nJ, t_chunk + sr.rJ + 16, t_end, t_fast, dJ);
   }
 }
 
@@ -555,6 +566,7 @@ template <int FORM>
 struct TileCtx {
   uint8_t* lds;
   const uint8_t* rows;  // channel's rows at the tile's first sample (uniform)
+  int t_fast;           // see fast_rows (uniform)
   long long row_stride;
   uint32_t offI, offJ;  // this thread's loads: its first I / J row and its inputs
   long long shiftI, shiftJ;  // time shifting: block delays in bytes (uniform)
@@ -665,7 +677,7 @@ struct RunList {
 // tile's accumulators and sums.  Returns the samples it integrated, padding
 // of a ragged last chunk included (padded samples are the code 8 + 8i).
 // R: the wave's role (see Role; fixed per wave, see tile_body).
-template <int FORM, bool ALIGNED, bool DEEP, class R>
+template <int FORM, bool FAST, bool DEEP, class R>
 __device__ __forceinline__ int tile_range(TileCtx<FORM>& x, const uint8_t* __restrict__ samples,
                                           int N, int f, int nI, int nJ, int t_begin, int t_end,
                                           uint8_t* lds) {
@@ -677,7 +689,8 @@ __device__ __forceinline__ int tile_range(TileCtx<FORM>& x, const uint8_t* __res
   x.rows = rows;
 
   // Steady state over the chunks whose loads all lie inside the frame.
-  const int nfast = ALIGNED ? len / KC : 0;
+  const int len_fast = FAST ? min(t_end, x.t_fast) - t_begin : 0;
+  const int nfast = len_fast > 0 ? len_fast / KC : 0;
   const int nsteady = nfast & ~1;
   int c = 0;
   if (nsteady >= 2) {
@@ -689,12 +702,12 @@ __device__ __forceinline__ int tile_range(TileCtx<FORM>& x, const uint8_t* __res
   // ranges), one buffer flip per chunk.
   v4i raw[4];
   auto load = [&](int cc) {
-    if (ALIGNED && (cc + 1) * KC <= len)
+    if (FAST && (cc + 1) * KC <= len_fast)
       load_pieces_fast<R::NP>(raw, rows + (long long)cc * KC * row_stride, row_stride, x.offI,
                               x.offJ, x.shiftI, x.shiftJ);
     else
       load_pieces_edge<R::NP>(raw, samples, row_stride, f, N, nI, nJ, x.sr, t_begin + cc * KC,
-                              t_end, x.dI, x.dJ);
+                              t_end, x.t_fast, x.dI, x.dJ);
   };
   if (c < nchunks) {
     load(c);
@@ -715,17 +728,17 @@ __device__ __forceinline__ int tile_range(TileCtx<FORM>& x, const uint8_t* __res
 }
 
 // All ranges of a tile for one wave role.
-template <int FORM, bool ALIGNED, bool DEEP, class R, class Ranges>
+template <int FORM, bool FAST, bool DEEP, class R, class Ranges>
 __device__ __forceinline__ int tile_ranges(TileCtx<FORM>& x, const uint8_t* __restrict__ samples,
                                            int N, int f, int nI, int nJ, const Ranges& rg,
                                            uint8_t* lds) {
   if constexpr (Ranges::kSingle) {
-    return tile_range<FORM, ALIGNED, DEEP, R>(x, samples, N, f, nI, nJ, rg.begin(0), rg.end(0),
+    return tile_range<FORM, FAST, DEEP, R>(x, samples, N, f, nI, nJ, rg.begin(0), rg.end(0),
                                               lds);
   } else {
     int teff = 0;
     for (int r = 0; r < rg.count(); ++r)
-      teff += tile_range<FORM, ALIGNED, DEEP, R>(x, samples, N, f, nI, nJ, rg.begin(r),
+      teff += tile_range<FORM, FAST, DEEP, R>(x, samples, N, f, nI, nJ, rg.begin(r),
                                                  rg.end(r), lds);
     return teff;
   }
@@ -749,8 +762,8 @@ static_assert(2 * EPI_SWAP <= EPI_PART, "epilogue regions overlap");
 // 2^24 (exact).  Int8 form: the caller keeps them <= XENG_I8_SEG_MAX, so that
 // the int32 sums of codes stay below 2 * 225 * 2^19 < 2^31.
 //
-// ALIGNED: N % 16 == 0 and the sample rows are 16-byte aligned, so that whole
-// chunks can take the fast loads.  DEEP: prefetch two chunks ahead (else one).
+// FAST: F N <= 2^25, so that whole chunks can take the fast loads.  DEEP:
+// prefetch two chunks ahead (else one).
 //
 // Wave roles.  Off the diagonal (I < J), wave (wr, wc) computes the 64 x 64
 // sub-tile (wr, wc) and sums A fragment wc and B fragment wr, so that the
@@ -775,12 +788,12 @@ static_assert(2 * EPI_SWAP <= EPI_PART, "epilogue regions overlap");
 // from the history the caller keeps in front of `samples`.  A block's largest
 // delay moves its (scalar) load base back; a lane's offset adds back the rows
 // its own segment is delayed less.  NULL tables: no shift.
-template <int FORM, bool ALIGNED, bool DEEP, bool SHIFT, class Ranges, bool SPLITDIAG = true,
+template <int FORM, bool FAST, bool DEEP, bool SHIFT, class Ranges, bool SPLITDIAG = true,
           bool WIDE = false>
 __device__ __forceinline__ void tile_body(const uint8_t* __restrict__ samples, int32_t* vis,
                                           int N, long long row_stride, long long NB, int f,
                                           int I, int J, const Ranges& rg, int mode,
-                                          uint8_t* lds, const int* seg_delay = nullptr,
+                                          uint8_t* lds, int t_fast, const int* seg_delay = nullptr,
                                           const int* blk_delay = nullptr) {
   // the wave index is uniform per wave: read it into a scalar register so that
   // every branch on it is a uniform one.  The thread index passes through an
@@ -810,10 +823,10 @@ __device__ __forceinline__ void tile_body(const uint8_t* __restrict__ samples, i
   // two J pieces
   TileCtx<FORM> x(tid);
   const int nI = I * BT + 16 * x.sr.seg, nJ = J * BT + 16 * x.sr.seg;
-  // the lane's load offsets; fast loads of inputs past N (edge tiles,
-  // N % 16 == 0) read a valid row instead: their LDS rows only reach
-  // baselines past N, never written
+  // the lane's load offsets; fast loads of pieces past N (edge tiles) read
+  // input 0 instead: their LDS rows only reach baselines past N, never written
   x.lds = lds;
+  x.t_fast = t_fast;
   x.row_stride = row_stride;
   int DI = 0, DJ = 0;
   x.dI = x.dJ = 0;
@@ -852,7 +865,7 @@ __device__ __forceinline__ void tile_body(const uint8_t* __restrict__ samples, i
   // around one, costs the compiler many registers)
   int teff;
 #define XENG_RANGES(...) \
-  tile_ranges<FORM, ALIGNED, DEEP, Role<__VA_ARGS__>>(x, samples, N, f, nI, nJ, rg, lds)
+  tile_ranges<FORM, FAST, DEEP, Role<__VA_ARGS__>>(x, samples, N, f, nI, nJ, rg, lds)
   if (diag) {
     switch (wave) {
       case 1: teff = XENG_RANGES(-1, -1, 1, false, true); break;
@@ -961,11 +974,11 @@ __device__ __forceinline__ void tile_body(const uint8_t* __restrict__ samples, i
   __syncthreads();  // the corrections are read before the LDS is reused
 }
 
-// Launch K<FORM, ALIGNED, SHIFT> for the run-time form, alignment and shift.
-#define XENG_DISPATCH3(K, form, aligned, shift, g, b, stream, arg)                            \
+// Launch K<FORM, FAST, SHIFT> for the run-time form, loads and shift.
+#define XENG_DISPATCH3(K, form, fast, shift, g, b, stream, arg)                            \
   do {                                                                                        \
     if ((form) == FORM_I8) {                                                                  \
-      if (aligned) {                                                                          \
+      if (fast) {                                                                             \
         if (shift) hipLaunchKernelGGL((K<FORM_I8, true, true>), g, b, 0, stream, arg);        \
         else hipLaunchKernelGGL((K<FORM_I8, true, false>), g, b, 0, stream, arg);             \
       } else {                                                                                \
@@ -973,7 +986,7 @@ __device__ __forceinline__ void tile_body(const uint8_t* __restrict__ samples, i
         else hipLaunchKernelGGL((K<FORM_I8, false, false>), g, b, 0, stream, arg);            \
       }                                                                                       \
     } else {                                                                                  \
-      if (aligned) {                                                                          \
+      if (fast) {                                                                             \
         if (shift) hipLaunchKernelGGL((K<FORM_F8, true, true>), g, b, 0, stream, arg);        \
         else hipLaunchKernelGGL((K<FORM_F8, true, false>), g, b, 0, stream, arg);             \
       } else {                                                                                \

@@ -12,7 +12,7 @@ namespace xeng {
 // exact integration may: the host then splits it into work gates that add
 // atomically (GatedArgs).  Consecutive logical ids are the tiles of one
 // (work gate, channel), which share samples.
-template <int FORM, bool ALIGNED, bool SHIFT>
+template <int FORM, bool FAST, bool SHIFT>
 __global__ void __launch_bounds__(NTHREADS, 2) xcorr_gated_kernel(GatedArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
   const int logical = xcd_logical_id(blockIdx.x, gridDim.x);
@@ -28,18 +28,19 @@ __global__ void __launch_bounds__(NTHREADS, 2) xcorr_gated_kernel(GatedArgs a) {
   // a work item may stand for part of a gate's runs: it then writes into that
   // gate's buffer, in its own write mode (see GatedArgs)
   const int2 vg = a.vgate ? a.vgate[g] : make_int2(g, a.write_mode);
-  tile_body<FORM, ALIGNED, false, SHIFT>(a.samples, a.vis + (long long)vg.x * a.F * NB * 2, a.N,
+  tile_body<FORM, FAST, false, SHIFT>(a.samples, a.vis + (long long)vg.x * a.F * NB * 2, a.N,
                                          a.row_stride, NB, f, I, J,
-                                         RunList{a.runs + r0, r1 - r0}, vg.y, lds, a.seg_delay,
+                                         RunList{a.runs + r0, r1 - r0}, vg.y, lds,
+                                         fast_rows(a.t_frame, a.N, f, a.F), a.seg_delay,
                                          a.blk_delay);
 }
 
-hipError_t launch_gated(const GatedArgs& a, int form, bool aligned, hipStream_t stream) {
+hipError_t launch_gated(const GatedArgs& a, int form, bool fast, hipStream_t stream) {
   const long long grid = (long long)a.F * a.tiles_per_chan * a.G;
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), b(NTHREADS);
-  XENG_DISPATCH3(xcorr_gated_kernel, form, aligned, a.seg_delay != nullptr, g, b, stream, a);
+  XENG_DISPATCH3(xcorr_gated_kernel, form, fast, a.seg_delay != nullptr, g, b, stream, a);
   return hipGetLastError();
 }
 

@@ -56,10 +56,10 @@ __device__ __forceinline__ void wide_load_edge(WideRaw& raw, const uint8_t* __re
                                                int nJ, int tI, int tJ, int t_end) {
 #pragma unroll
   for (int k = 0; k < 2; ++k)
-    raw.i[k] = load_piece_edge(samples, row_stride, f, N, nI, tI + 32 * k, t_end);
+    raw.i[k] = load_piece_edge(samples, row_stride, f, N, nI, tI + 32 * k, t_end, t_end);
 #pragma unroll
   for (int k = 0; k < 4; ++k)
-    raw.j[k] = load_piece_edge(samples, row_stride, f, N, nJ, tJ + 16 * k, t_end);
+    raw.j[k] = load_piece_edge(samples, row_stride, f, N, nJ, tJ + 16 * k, t_end, t_end);
 }
 
 template <int FORM>

@@ -184,6 +184,10 @@ long long tiles_per_channel(int N) {
   return nt * (nt + 1) / 2;
 }
 
+// Fast loads: 16-byte row pieces at any alignment, with per-lane offsets (64
+// rows) that fit 31 bits.
+bool fast_loads(int F, int N) { return (long long)F * N <= (1LL << 25); }
+
 // 128 x 256 tiles (I, J) with J >= I / 2.
 long long wide_tiles_per_channel(int N) {
   const long long nI = (N + kTile - 1) / kTile, nJ = (N + 2 * kTile - 1) / (2 * kTile);
@@ -664,16 +668,15 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   }
 
   const int nt = (N + kTile - 1) / kTile;
-  // fast loads: 16-byte row pieces, and per-lane offsets that fit 32 bits
-  const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0) &&
-                       ((long long)F * N <= (1LL << 25));
+  const bool fast = fast_loads(F, N);
+  const bool aligned = fast && (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0);
   // wide tiles (128 x 256, one workgroup per CU) only on request and when
   // the rows allow fast loads; 128 x 128 (two workgroups per CU) otherwise
   const bool wide = aligned && p->kernel == 2 && !kshift;
   // the channel kernel (int8, N <= 256): on request, or automatically above
-  // one tile edge when the rows allow fast loads
+  // one tile edge
   const bool chan = p->form == XENG_FORM_I8 && !kshift && N <= kChanMax &&
-                    (p->kernel == 5 || (p->kernel == 0 && N > kTile && aligned));
+                    (p->kernel == 5 || (p->kernel == 0 && N > kTile && fast));
   const long long tpc = wide ? wide_tiles_per_channel(N) : tiles_per_channel(N);
   const int occupancy = wide ? 1 : kOccupancy;
   // The FP8 form integrates at most XENG_F8_FLUSH_MAX samples per launch (f32
@@ -707,11 +710,12 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       c.nslices = ns;
       c.slice_len = sl;
       c.row_stride = (long long)F * N;
+      c.t_frame = T;
       // one slice writes vis itself; several store their own triangles into
       // the workspace, and a second kernel sums them into vis
       c.partial = ns > 1 ? p->d_chan_ws : nullptr;
       c.write_mode = (ns == 1 && add) ? xeng::WM_ADD : xeng::WM_STORE;
-      hipError_t e = xeng::launch_chan(c, aligned, s);
+      hipError_t e = xeng::launch_chan(c, fast, s);
       if (e != hipSuccess) return hip_fail(p, e, "channel kernel launch");
       if (ns > 1) {
         e = xeng::launch_chan_reduce(p->d_chan_ws, vis, part, ns, add, s);
@@ -766,6 +770,7 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
     a.nslices = nslices;
     a.slice_len = slice_len;
     a.row_stride = (long long)F * N;
+    a.t_frame = T;
     a.head_tiles = (int)head;
     a.tail_slices = tail_slices;
     a.tail_len = tail_len;
@@ -790,7 +795,7 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       hipError_t e = xeng::launch_zero_tiles(vis, N, (int)tpc, nt, (int)head, (int)(W - head), s);
       if (e != hipSuccess) return hip_fail(p, e, "tail zero launch");
     }
-    hipError_t e = wide ? xeng::launch_wide(a, p->form, s) : xeng::launch_tiles(a, p->form, aligned, s);
+    hipError_t e = wide ? xeng::launch_wide(a, p->form, s) : xeng::launch_tiles(a, p->form, fast, s);
     if (e != hipSuccess) return hip_fail(p, e, "correlation kernel launch");
   }
   return p->shift ? mark_tables(p, s) : XENG_OK;
@@ -898,8 +903,6 @@ int xeng_correlate_gated(xeng_plan_t p, const uint8_t* samples, int N, int F, in
     if (e != hipSuccess) return hip_fail(p, e, "shift copy launch");
     samples = p->d_shifted;
   }
-  const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0) &&
-                       ((long long)F * N <= (1LL << 25));
   // split gates that overwrite: their buffers are cleared first (the buffers
   // of consecutive gates are contiguous in the gate-major output)
   const long long gate_words = (long long)F * N * (N + 1);
@@ -928,11 +931,12 @@ int xeng_correlate_gated(xeng_plan_t p, const uint8_t* samples, int N, int F, in
     a.runs = p->d_runs;
     a.vgate = p->d_vgate + (p->seg_goff[k] - k);
     a.row_stride = (long long)F * N;
+    a.t_frame = T;
     a.seg_delay = kshift ? p->d_seg_delay : nullptr;
     a.blk_delay = kshift ? p->d_blk_delay : nullptr;
     // adding: a work gate without runs adds nothing
     a.skip_empty = a.write_mode == xeng::WM_ADD ? 1 : 0;
-    e = xeng::launch_gated(a, p->form, aligned, s);
+    e = xeng::launch_gated(a, p->form, fast_loads(F, N), s);
     if (e != hipSuccess) return hip_fail(p, e, "gated correlation kernel launch");
   }
   return p->shift ? mark_tables(p, s) : XENG_OK;
@@ -998,7 +1002,6 @@ int xeng_correlate_flagged(xeng_plan_t p, uint8_t* samples, const uint32_t* flag
   int rc = xeng_correlate(p, samples, N, F, T, vis, stream);
   if (rc != XENG_OK) return rc;
   // the event rows: Re X_ij = rows where i and j are both invalid
-  const bool aligned = (N % 16 == 0) && ((long long)F * N <= (1LL << 25));
   for (int k = 0; k < nseg; ++k) {
     xeng::GatedArgs g;
     g.samples = p->d_fU;
@@ -1012,11 +1015,12 @@ int xeng_correlate_flagged(xeng_plan_t p, uint8_t* samples, const uint32_t* flag
     g.gate_off = a.fgate_off + 2 * k;
     g.runs = p->d_fruns;
     g.row_stride = (long long)F * N;
+    g.t_frame = (int)p->flag_cap;
     g.seg_delay = nullptr;
     g.blk_delay = nullptr;
     g.vgate = nullptr;
     g.skip_empty = 1;
-    e = xeng::launch_gated(g, XENG_FORM_I8, aligned, s);
+    e = xeng::launch_gated(g, XENG_FORM_I8, fast_loads(F, N), s);
     if (e != hipSuccess) return hip_fail(p, e, "event correlation kernel launch");
   }
   e = xeng::launch_flag_counts(a, p->accumulate ? 1 : 0, s);
@@ -1194,7 +1198,7 @@ int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, uns
               it.t0 = s * len;
               it.t1 = std::min(d.T, (s + 1) * len);
               it.mode = mode;
-              it.pad = 0;
+              it.t_fast = xeng::fast_rows(d.T, d.N, f, d.F);
               // cost: MFMA blocks that hold baselines x samples
               const int rows = std::min(kTile, d.N - I * kTile);
               const int cols = std::min(kTile, d.N - J * kTile);
@@ -1266,8 +1270,7 @@ static int batch_upload(xeng_plan_t p, const uint8_t* const* samples, int32_t* c
     b.N = d.N;
     b.F = d.F;
     b.T = d.T;
-    b.aligned = (d.N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples[k]) & 15) == 0) &&
-                ((long long)d.F * d.N <= (1LL << 25));
+    b.fast = fast_loads(d.F, d.N);
     b.zero = samples[k] ? p->inst_zero[k] : 0;
     b.pad = 0;
     p->uploaded[2 * k] = samples[k];
@@ -1401,8 +1404,6 @@ int xeng_correlate_batch_noalloc(const xeng_instance* descs, int count, unsigned
     const int mode = (S > 1 || shared) ? xeng::WM_ATOMIC
                                        : (accumulate ? xeng::WM_ADD : xeng::WM_STORE);
     const bool zero = S > 1 && !accumulate;
-    const bool aligned = (d.N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples[k]) & 15) == 0) &&
-                         ((long long)d.F * d.N <= (1LL << 25));
     in.samples = samples[k];
     in.vis = vis[k];
     in.N = d.N;
@@ -1410,7 +1411,7 @@ int xeng_correlate_batch_noalloc(const xeng_instance* descs, int count, unsigned
     in.T = d.T;
     in.S = S;
     in.len = len;
-    in.flags = mode | (zero ? 4 : 0) | (aligned ? 8 : 0);
+    in.flags = mode | (zero ? 4 : 0) | (fast_loads(d.F, d.N) ? 8 : 0);
     in.first = 0;
     in.pad = 0;
     any_zero |= zero;

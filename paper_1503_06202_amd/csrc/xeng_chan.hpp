@@ -17,13 +17,14 @@ struct ChanArgs {
   int nslices, slice_len;  // slice_len a multiple of 64
   int write_mode;          // WM_STORE or WM_ADD into vis; WM_STORE into partial
   long long row_stride;    // F * N
+  int t_frame;             // rows of the frame (no read passes its end)
   // with several slices: slice s stores its own sums into
   // partial + s F N(N+1) (same layout as vis), for launch_chan_reduce
   int32_t* partial;
 };
 
-// aligned: fast 16-byte loads (N % 16 == 0, 16-byte aligned rows, F N <= 2^25)
-hipError_t launch_chan(const ChanArgs& a, bool aligned, hipStream_t stream);
+// fast: F N <= 2^25 (the offsets of 64 rows fit 31 bits)
+hipError_t launch_chan(const ChanArgs& a, bool fast, hipStream_t stream);
 
 // vis[i] (+)= sum over s < ns of partial[s n + i], i < n (add: accumulate)
 hipError_t launch_chan_reduce(const int32_t* partial, int32_t* vis, long long n, int ns, bool add,

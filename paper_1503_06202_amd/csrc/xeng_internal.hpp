@@ -13,6 +13,13 @@ namespace xeng {
 // 32-bit ones (see put_pairs in xcorr_device.hpp).
 enum WriteMode { WM_STORE = 0, WM_ADD = 1, WM_ATOMIC = 2, WM_ATOMIC64 = 3 };
 
+// Rows of a T-row frame whose 16-byte pieces may all be read in channel f of F:
+// the last piece of a row of N inputs may reach into the next channel or row,
+// which the frame's very last row does not have.
+__host__ __device__ inline int fast_rows(int T, int N, int f, int F) {
+  return T - ((N & 15) && f == F - 1 ? 1 : 0);
+}
+
 // Arguments of the tile kernel: one frame, all channels.
 struct TileArgs {
   const uint8_t* samples;  // device [T][F][N]
@@ -25,6 +32,7 @@ struct TileArgs {
   int slice_len;       // samples per slice, a multiple of 64
   int write_mode;      // WM_STORE, WM_ADD or WM_ATOMIC: head items
   long long row_stride;  // F * N: bytes between consecutive time rows
+  int t_frame;           // rows of the frame (no read passes its end)
   // Tiles are numbered g = f * tiles_per_chan + p.  Head tiles [0, head_tiles)
   // run as nslices slices each; the remaining (tail) tiles as tail_slices
   // slices of tail_len samples each, adding with int32 atomics (tail_mode).
@@ -43,7 +51,8 @@ struct TileArgs {
   int split_diag;
 };
 
-hipError_t launch_tiles(const TileArgs& a, int form, bool aligned, hipStream_t stream);
+// fast: F N <= 2^25 (the offsets of 64 rows fit 31 bits)
+hipError_t launch_tiles(const TileArgs& a, int form, bool fast, hipStream_t stream);
 
 // Output gating: every (channel, tile, work gate g) integrates the runs
 // runs[gate_off[g] .. gate_off[g + 1]) (absolute [begin, end) sample ranges)
@@ -62,12 +71,13 @@ struct GatedArgs {
   const int2* runs;       // device [gate_off[G]]
   const int2* vgate;      // device [G] (output gate, write mode), or NULL
   long long row_stride;
+  int t_frame;            // as in TileArgs
   const int* seg_delay;   // time shifting, as in TileArgs
   const int* blk_delay;
   int skip_empty;         // 1: a gate without runs leaves its output untouched
 };
 
-hipError_t launch_gated(const GatedArgs& a, int form, bool aligned, hipStream_t stream);
+hipError_t launch_gated(const GatedArgs& a, int form, bool fast, hipStream_t stream);
 // Clear the visibilities of tiles [first, first + count) (numbered as in
 // TileArgs) before their slices add into them.
 hipError_t launch_zero_tiles(int32_t* vis, int N, int tiles_per_chan, int nt, int first, int count,
@@ -138,7 +148,7 @@ struct BatchItem {
   int I, J;   // tile
   int t0, t1; // time range
   int mode;   // write mode
-  int pad;
+  int t_fast; // see fast_rows
 };
 
 // Per-instance descriptor on the device.
@@ -146,7 +156,7 @@ struct BatchInst {
   const uint8_t* samples;  // device [T][F][N]
   int32_t* vis;            // device [F][N(N+1)/2][2]
   int N, F, T;
-  int aligned;  // N % 16 == 0, samples 16-byte aligned, F * N <= 2^26
+  int fast;     // F * N <= 2^25: fast loads
   int zero;     // clear vis before the launch (its tiles are integrated by atomic adds)
   int pad;
 };

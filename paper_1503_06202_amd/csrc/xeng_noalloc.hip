@@ -38,7 +38,7 @@ __global__ void noalloc_prep_kernel(NoallocArgs a) {
     b.N = in.N;
     b.F = in.F;
     b.T = in.T;
-    b.aligned = (in.flags >> 3) & 1;
+    b.fast = (in.flags >> 3) & 1;
     b.zero = (in.flags >> 2) & 1;
     b.pad = 0;
     insts[gid] = b;
@@ -57,7 +57,7 @@ __global__ void noalloc_prep_kernel(NoallocArgs a) {
     it.t0 = s * in.len;
     it.t1 = min(in.T, (s + 1) * in.len);
     it.mode = in.flags & 3;
-    it.pad = 0;
+    it.t_fast = fast_rows(in.T, in.N, it.f, in.F);
     items[i] = it;
   }
 }
