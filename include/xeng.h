@@ -109,9 +109,10 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * "Full Correlation"; Eq. (1)) on the offset-binary samples of Sec. II-A.
  * N and F must equal the plan's, 1 <= T <= T_max.  With XENG_ACCUMULATE in the
  * plan, the frame's sums are added to vis; otherwise vis is overwritten.
- * The channel kernel (see xeng_plan_set_tuning) with S > 1 time slices keeps
- * the slices' partial outputs, S F N(N+1) int32, in plan-owned device memory
- * allocated on first use (grown, after the plan's last call, when S grows).
+ * The small-array and channel kernels (see xeng_plan_set_tuning) with S > 1
+ * time slices keep the slices' partial outputs, S F N(N+1) int32, in plan-owned
+ * device memory allocated on first use (grown, after the plan's last call, when
+ * S grows).
  * Frames of more than 640 inputs and enough work take the packed path (unless
  * the plan names a kernel): the samples are repacked into FP6 operands (the
  * 4-bit codes are FP6 numbers as they stand) and correlated on FP6 matrix
@@ -119,8 +120,9 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * operands (1.5 bytes a sample of one segment) and the partial outputs of
  * sliced tiles are plan-owned device memory, allocated on first use: at most 4
  * GiB of operands (or one channel's), larger frames run in groups of channels.
- * A call under HIP graph capture, or one for which that memory cannot be
- * allocated, takes the tile kernels.
+ * A call under HIP graph capture that needs any of this memory, or one for
+ * which it cannot be allocated, takes the tile kernels.  Calls of one plan on
+ * several streams take turns with that memory: the library orders them.
  * Errors: XENG_EINVAL (NULL plan or pointer, T < 1), XENG_EPLAN (N or F differ
  * from the plan, T > T_max), XENG_EOVERFLOW (T > XENG_T_EXACT_MAX),
  * XENG_ENOMEM (that memory cannot be allocated), XENG_EHIP.
@@ -146,10 +148,13 @@ int xeng_correlate(xeng_plan_t p, const uint8_t *samples, int N, int F, int T,
  *            waves per (channel, time slice) covers the whole triangle of a
  *            channel of at most 256 inputs, each sample read once; several
  *            time slices store partial outputs that a second kernel sums
- *            into vis (int8 form only; the FP8 form, time shifting through
- *            the loads and N > 256 use 1).  Automatic: 5 for the int8 form at
- *            128 < N <= 256 (F N <= 2^25), the packed path (see
- *            xeng_correlate) on large frames of more than 640 inputs, else 1,
+ *            into vis (on request int8 form only; the FP8 form, time shifting
+ *            through the loads and N > 256 use 1).  Automatic, both forms: the
+ *            small-array kernel at N <= 128 (whole channels of 16, 32, 64 or
+ *            128 columns per workgroup), the channel kernel at 128 < N <= 256
+ *            (F N <= 2^25), both without shifting in the loads; the packed
+ *            path (see xeng_correlate) on large frames of more than 640 inputs;
+ *            else 1,
  *            the fastest on gfx950 at the measured sizes; the autotuner
  *            (tune.tune_plain) picks per shape.
  * Errors: XENG_EINVAL (NULL plan, negative split_t, kernel outside 0..5).

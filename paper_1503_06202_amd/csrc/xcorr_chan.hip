@@ -30,6 +30,8 @@
 // fills a CU; a launch is one workgroup per (channel, time slice).  With
 // several slices, each stores its own partial triangles and
 // chan_reduce_kernel sums them into vis.
+#include <algorithm>
+
 #include "xcorr_device.hpp"
 #include "xeng_chan.hpp"
 
@@ -537,26 +539,52 @@ __global__ void __launch_bounds__(CH_THREADS, 1) xcorr_chan_kernel(ChanArgs a) {
 // costs less than the slices adding into vis with atomics after a fill (every
 // workgroup of the channel kernel finishes at once, so nothing would hide the
 // atomics).
-__global__ void chan_reduce_kernel(const int32_t* __restrict__ part, int32_t* __restrict__ vis,
-                                   long long n, int ns, int add) {
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((n & 3) == 0 && !(reinterpret_cast<uintptr_t>(vis) & 15)) {
-    const long long n4 = n >> 2;
-    const v4i* p4 = reinterpret_cast<const v4i*>(part);
-    v4i* v4 = reinterpret_cast<v4i*>(vis);
-    for (; i < n4; i += stride) {
-      v4i acc = p4[i];
-      for (int s = 1; s < ns; ++s) acc += p4[s * n4 + i];
-      if (add) acc += v4[i];
-      v4[i] = acc;
+//
+// G: threads that share one 16-byte output, each summing every G-th slice.
+// G = 1 streams; where the outputs alone are too few to fill the GPU, G = 8
+// keeps the chain of loads short (64 inputs, 4 channels, 32 slices: 4160
+// outputs).
+template <int G>
+__global__ void __launch_bounds__(256) chan_reduce_kernel(const int32_t* __restrict__ part,
+                                                          int32_t* __restrict__ vis, long long n,
+                                                          int ns, int add) {
+  constexpr int PER = 256 / G;  // outputs per workgroup and round
+  __shared__ v4i sh[G > 1 ? 256 : 1];
+  const long long n4 = n >> 2;
+  const v4i* p4 = reinterpret_cast<const v4i*>(part);
+  v4i* v4 = reinterpret_cast<v4i*>(vis);
+  const int o = threadIdx.x % PER, g = threadIdx.x / PER;
+  for (long long base = (long long)blockIdx.x * PER; base < n4; base += (long long)gridDim.x * PER) {
+    const long long i = base + o;
+    v4i acc = v4i{0, 0, 0, 0};
+    if (i < n4) {
+#pragma unroll 4
+      for (int s = g; s < ns; s += G) acc += p4[s * n4 + i];
     }
-  } else {
-    for (; i < n; i += stride) {
-      int acc = part[i];
-      for (int s = 1; s < ns; ++s) acc += part[s * n + i];
-      vis[i] = add ? vis[i] + acc : acc;
+    if (G > 1) {
+      __syncthreads();
+      sh[threadIdx.x] = acc;
+      __syncthreads();
+      if (g > 0) continue;  // no barrier below: the next round's first one orders the reads
+#pragma unroll
+      for (int k = 1; k < G; ++k) acc += sh[k * PER + o];
     }
+    if (i >= n4) continue;
+    if (add) acc += v4[i];
+    v4[i] = acc;
+  }
+}
+
+// The same an int at a time, where vis is not 16-byte aligned or n not a
+// multiple of 4.
+__global__ void __launch_bounds__(256) chan_reduce1_kernel(const int32_t* __restrict__ part,
+                                                           int32_t* __restrict__ vis, long long n,
+                                                           int ns, int add) {
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
+    int acc = add ? vis[i] : 0;
+#pragma unroll 8
+    for (int s = 0; s < ns; ++s) acc += part[s * n + i];
+    vis[i] = acc;
   }
 }
 
@@ -564,10 +592,16 @@ hipError_t launch_chan_reduce(const int32_t* partial, int32_t* vis, long long n,
                               hipStream_t stream) {
   if (n <= 0) return hipSuccess;
   if (ns < 1) return hipErrorInvalidValue;
-  long long blocks = ((n >> 2) + 255) / 256;
-  blocks = blocks < 1 ? 1 : (blocks > 4096 ? 4096 : blocks);
-  hipLaunchKernelGGL(chan_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, partial,
-                     vis, n, ns, add ? 1 : 0);
+  const bool vec = (n & 3) == 0 && !(reinterpret_cast<uintptr_t>(vis) & 15);
+  const int G = vec && ns >= 8 && (n >> 2) < 256 * 512 ? 8 : 1;
+  const long long per = vec ? 256 / G : 256, total = vec ? n >> 2 : n;
+  const dim3 grid((unsigned)std::min<long long>(4096, (total + per - 1) / per)), b(256);
+  if (!vec)
+    hipLaunchKernelGGL(chan_reduce1_kernel, grid, b, 0, stream, partial, vis, n, ns, add ? 1 : 0);
+  else if (G == 8)
+    hipLaunchKernelGGL(chan_reduce_kernel<8>, grid, b, 0, stream, partial, vis, n, ns, add ? 1 : 0);
+  else
+    hipLaunchKernelGGL(chan_reduce_kernel<1>, grid, b, 0, stream, partial, vis, n, ns, add ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -83,20 +83,13 @@ struct xeng_plan_s {
   std::vector<int> gate_zero;              // gates to clear before a split gate adds into them
   std::vector<int> seg_goff, seg_nvg;      // per launch segment: first table entry, work gates
 
-  // channel kernel with time slices: the slices' partial triangles (plan-owned,
-  // grown on demand) and the event of the last call that read them
-  int32_t* d_chan_ws = nullptr;
-  size_t chan_ws_ints = 0;
-  hipEvent_t chan_ws_used = nullptr;
-  bool chan_ws_pending = false;
-
-  // packed path: operands and code sums of a segment of a channel group
-  // (plan-owned, allocated on first use) and the event of the last call that
-  // read them
-  uint8_t* d_packed = nullptr;
-  size_t packed_bytes = 0;
-  hipEvent_t packed_used = nullptr;
-  bool packed_pending = false;
+  // workspace of the calls that need one (partial outputs of time slices,
+  // packed operands): plan-owned, grown on demand; see workspace()
+  uint8_t* d_ws = nullptr;
+  size_t ws_bytes = 0;
+  bool ws_pending = false;        // a call has used it
+  hipStream_t ws_stream = nullptr;  // the stream of those calls, until a second one appears
+  hipEvent_t ws_used = nullptr;   // from then on: recorded after every use
 
   // time shifting (xeng_plan_set_delays): per-segment delays and block maxima
   bool shift = false;
@@ -393,36 +386,55 @@ int xeng_plan_set_tuning(xeng_plan_t p, int split_t, int kernel) {
 
 const char* xeng_plan_error(xeng_plan_t p) { return p ? p->err.c_str() : ""; }
 
-// The channel kernel's slice workspace, at least `ints` int32: grown when
-// needed (after the plan's last call that read it has finished), and ordered
-// after that call on `s` when it may still run on another stream.
-static int chan_workspace(xeng_plan_t p, size_t ints, hipStream_t s) {
+// The plan's workspace, at least `bytes`, for a call on `s`: grown when needed
+// (after the plan's calls have finished), and ordered after the last call that
+// used it.  Calls on one stream are in order anyway, and an event recorded
+// after each of them costs more than a small frame (12.2 us a call with, 7.4
+// without, 16 inputs and 256 samples in two slices).  So a plan records none
+// until a call arrives on a second stream; that call waits once, on the host,
+// for the device, and from then on every use records an event that the next
+// one waits for on its stream.
+static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
   hipError_t e = hipSuccess;
-  if (!p->chan_ws_used) {
-    e = hipEventCreateWithFlags(&p->chan_ws_used, hipEventDisableTiming);
+  if (p->ws_pending && !p->ws_used && s != p->ws_stream) {
+    e = hipDeviceSynchronize();
+    if (e != hipSuccess) return hip_fail(p, e, "hipDeviceSynchronize");
+    e = hipEventCreateWithFlags(&p->ws_used, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(p, e, "hipEventCreate");
+    p->ws_pending = false;
   }
-  if (ints > p->chan_ws_ints) {
-    if (p->chan_ws_pending) {
-      e = hipEventSynchronize(p->chan_ws_used);
-      if (e != hipSuccess) return hip_fail(p, e, "hipEventSynchronize");
-      p->chan_ws_pending = false;
+  if (bytes > p->ws_bytes) {
+    if (p->ws_pending) {
+      e = hipDeviceSynchronize();
+      if (e != hipSuccess) return hip_fail(p, e, "hipDeviceSynchronize");
+      p->ws_pending = false;
     }
-    if (p->d_chan_ws) (void)hipFree(p->d_chan_ws);
-    p->d_chan_ws = nullptr;
-    p->chan_ws_ints = 0;
-    e = hipMalloc((void**)&p->d_chan_ws, ints * sizeof(int32_t));
+    if (p->d_ws) (void)hipFree(p->d_ws);
+    p->d_ws = nullptr;
+    p->ws_bytes = 0;
+    e = hipMalloc((void**)&p->d_ws, bytes);
     if (e != hipSuccess) {
-      p->d_chan_ws = nullptr;
+      p->d_ws = nullptr;
       (void)hipGetLastError();
       if (e == hipErrorOutOfMemory) return XENG_ENOMEM;
-      return hip_fail(p, e, "hipMalloc (slice workspace)");
+      return hip_fail(p, e, "hipMalloc (workspace)");
     }
-    p->chan_ws_ints = ints;
-  } else if (p->chan_ws_pending) {
-    e = hipStreamWaitEvent(s, p->chan_ws_used, 0);
+    p->ws_bytes = bytes;
+  } else if (p->ws_pending && p->ws_used) {
+    e = hipStreamWaitEvent(s, p->ws_used, 0);
     if (e != hipSuccess) return hip_fail(p, e, "hipStreamWaitEvent");
   }
+  return XENG_OK;
+}
+
+// After a call's last kernel that uses the workspace.
+static int workspace_used(xeng_plan_t p, hipStream_t s) {
+  if (p->ws_used) {
+    const hipError_t e = hipEventRecord(p->ws_used, s);
+    if (e != hipSuccess) return hip_fail(p, e, "hipEventRecord");
+  }
+  p->ws_stream = s;
+  p->ws_pending = true;
   return XENG_OK;
 }
 
@@ -560,31 +572,8 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
   }
   hipError_t e = hipSuccess;
   const size_t operands = (per_chan * group + 255) / 256 * 256, need = operands + part;
-  if (!p->packed_used) {
-    e = hipEventCreateWithFlags(&p->packed_used, hipEventDisableTiming);
-    if (e != hipSuccess) return hip_fail(p, e, "hipEventCreate");
-  }
-  if (need > p->packed_bytes) {
-    if (p->packed_pending) {
-      e = hipEventSynchronize(p->packed_used);
-      if (e != hipSuccess) return hip_fail(p, e, "hipEventSynchronize");
-      p->packed_pending = false;
-    }
-    if (p->d_packed) (void)hipFree(p->d_packed);
-    p->d_packed = nullptr;
-    p->packed_bytes = 0;
-    e = hipMalloc((void**)&p->d_packed, need);
-    if (e != hipSuccess) {
-      p->d_packed = nullptr;
-      (void)hipGetLastError();
-      if (e == hipErrorOutOfMemory) return XENG_ENOMEM;
-      return hip_fail(p, e, "hipMalloc (packed operands)");
-    }
-    p->packed_bytes = need;
-  } else if (p->packed_pending) {
-    e = hipStreamWaitEvent(s, p->packed_used, 0);
-    if (e != hipSuccess) return hip_fail(p, e, "hipStreamWaitEvent");
-  }
+  int rc = workspace(p, need, s);
+  if (rc != XENG_OK) return rc;
   const long long row = (long long)F * N, NB2 = (long long)N * (N + 1);
   const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0);
   for (int t0 = 0; t0 < T; t0 += seg) {
@@ -605,8 +594,8 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
       const int plen = k.steps * xeng::PK_STEP;
       k.sumb = packed_sumb(blocks, nch, plen, p->cu_count);
       k.nsum = (plen + k.sumb - 1) / k.sumb;
-      k.packed = p->d_packed;
-      k.sums = reinterpret_cast<int2*>(p->d_packed +
+      k.packed = p->d_ws;
+      k.sums = reinterpret_cast<int2*>(p->d_ws +
                                        (size_t)nch * k.steps * blocks * xeng::BLOCK_BYTES);
       // delays that differ inside a block: by source windows
       k.seg_delay = p->shift ? p->d_seg_delay : nullptr;
@@ -621,7 +610,7 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
       a.packed = k.packed;
       a.sums = k.sums;
       a.vis = vis + f0 * NB2;
-      a.partial = part ? reinterpret_cast<int2*>(p->d_packed + operands) : nullptr;
+      a.partial = part ? reinterpret_cast<int2*>(p->d_ws + operands) : nullptr;
       a.N = N;
       a.nchan = nch;
       a.steps = k.steps;
@@ -639,10 +628,58 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
       if (e != hipSuccess) return hip_fail(p, e, "packed correlation launch");
     }
   }
-  e = hipEventRecord(p->packed_used, s);
-  if (e != hipSuccess) return hip_fail(p, e, "hipEventRecord");
-  p->packed_pending = true;
+  rc = workspace_used(p, s);
+  if (rc != XENG_OK) return rc;
   return p->shift ? mark_tables(p, s) : XENG_OK;
+}
+
+// Time slices of the channel kernel and the small-array kernel (workgroup
+// columns W of a channel, or of the channels that share a small-array
+// workgroup).  Microseconds, fitted to frames of 16..256 inputs in 1 to 32
+// slices (N = 64, F = 4, T = 8192: 33.9 in one, 13.5 in 8, 11.9 in 32; N = 64,
+// F = 256: 34.9 in one, 32.4 in 2, 44.4 in 8): an item takes `tau` per turn (a
+// chunk, or the four chunks that the waves of a small workgroup take at once);
+// items sharing a CU (up to `occ`) run at 1.7 times the rate of one, at 1.1
+// times on whole tile edges (N = 112, F = 46, T = 31552: 66.6 in 5 slices on
+// 230 CUs, 86 in 6 that put two on a few CUs, 66.3 in 11 with two on each); the
+// frame is read at 4.8 TB/s at best; slices store partial triangles and a second
+// launch sums them.
+struct Slices {
+  int n, len;
+};
+
+static Slices channel_slices(xeng_plan_t p, bool small, int N, int F, int len) {
+  const int chunks = (len + kChunk - 1) / kChunk;
+  const double part = (double)F * N * (N + 1) * sizeof(int32_t);
+  const int P = small ? xeng::small_columns(N) : 2 * kTile;
+  const int ch = small ? kTile / P : 1, turn = P < kTile ? 4 : 1;
+  const double tau = P < 64 ? 0.75 : P == 64 ? 0.96 : P == kTile ? 0.55 : 1.15;
+  const int occ = P < 64 ? 3 : P <= kTile ? 2 : 1;
+  const long long W = (F + ch - 1) / ch;
+  auto slices = [&](int n) {
+    const int per = (chunks + n - 1) / n;
+    return Slices{(chunks + per - 1) / per, per * kChunk};
+  };
+  if (p->split_t > 0) return slices(std::min(p->split_t, chunks));
+  Slices best = slices(1);
+  double cost = 1e300;
+  for (int n = 1; n <= std::min(64, (chunks + turn - 1) / turn); ++n) {
+    const Slices c = slices(n);
+    if (c.n != n) continue;
+    if (n > 1 && n * part > 512e6) break;
+    const long long items = W * n, slots = (long long)p->cu_count * occ;
+    const long long per_cu = (std::min(items, slots) + p->cu_count - 1) / p->cu_count;
+    const double item = (c.len / kChunk + turn - 1) / turn * tau *
+                        (per_cu > 1 ? per_cu / (P == kTile ? 1.1 : 1.7) : 1.0);
+    const double read = (double)F * N * len / 4.8e6;
+    const double t = 3.0 + std::max(read, (items + slots - 1) / slots * item) +
+                     (n > 1 ? 3.0 + 2.0 * n * part / 2.8e6 : 0.0);
+    if (t < cost) {
+      cost = t;
+      best = c;
+    }
+  }
+  return best;
 }
 
 int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, int32_t* vis,
@@ -673,10 +710,25 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   // wide tiles (128 x 256, one workgroup per CU) only on request and when
   // the rows allow fast loads; 128 x 128 (two workgroups per CU) otherwise
   const bool wide = aligned && p->kernel == 2 && !kshift;
-  // the channel kernel (int8, N <= 256): on request, or automatically above
-  // one tile edge
-  const bool chan = p->form == XENG_FORM_I8 && !kshift && N <= kChanMax &&
-                    (p->kernel == 5 || (p->kernel == 0 && N > kTile && fast));
+  // the small-array kernel: automatically up to one tile edge (both forms)
+  bool small = p->kernel == 0 && !kshift && N <= kTile;
+  // the channel kernel (N <= 256): on request (int8), or automatically above
+  // one tile edge (both forms: 222 us in int8 against 297 us on FP8 tiles, N =
+  // 256, F = 64, T = 32768)
+  bool chan = !kshift && N <= kChanMax &&
+              (p->kernel == 5 ? p->form == XENG_FORM_I8 : p->kernel == 0 && N > kTile && fast);
+  if (small || chan) {
+    // the slices' partial triangles, for the longest launch; a call that
+    // cannot have them (no memory, or under capture) takes the tile kernels
+    const int ns = channel_slices(p, small, N, F, std::min(T, XENG_I8_SEG_MAX)).n;
+    if (ns > 1) {
+      rc = stream_captures(s)
+               ? XENG_ENOMEM
+               : workspace(p, (size_t)ns * F * N * (N + 1) * sizeof(int32_t), s);
+      if (rc == XENG_ENOMEM) small = chan = false;
+      else if (rc != XENG_OK) return rc;
+    }
+  }
   const long long tpc = wide ? wide_tiles_per_channel(N) : tiles_per_channel(N);
   const int occupancy = wide ? 1 : kOccupancy;
   // The FP8 form integrates at most XENG_F8_FLUSH_MAX samples per launch (f32
@@ -684,22 +736,19 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   // most XENG_I8_SEG_MAX (int32 sums of codes below 2^31); later launches add
   // their sums in stream order.  The wide int8 kernel does the whole frame in
   // one launch.
-  const int seg = p->form == XENG_FORM_F8 ? XENG_F8_FLUSH_MAX : (wide ? T : XENG_I8_SEG_MAX);
+  const int seg = p->form == XENG_FORM_F8 && !small && !chan ? XENG_F8_FLUSH_MAX
+                  : wide                                           ? T
+                                                                   : XENG_I8_SEG_MAX;
   for (int t0 = 0; t0 < T; t0 += seg) {
     const int t1 = std::min(T, t0 + seg), len = t1 - t0;
-    if (chan) {
-      // one work item per (channel, slice), one workgroup per CU
-      int ns = p->split_t > 0 ? p->split_t : auto_slices(F, len, p->cu_count, 1);
-      ns = std::min(ns, (len + kChunk - 1) / kChunk);
-      int sl = (len + ns - 1) / ns;
-      sl = (sl + kChunk - 1) / kChunk * kChunk;
-      ns = (len + sl - 1) / sl;
+    if (chan || small) {
+      // a shorter last segment slices no finer than the first: its partial
+      // triangles fit
+      const Slices sc = channel_slices(p, small, N, F, len);
       const bool add = p->accumulate || t0 > 0;
       const long long part = (long long)F * N * (N + 1);  // ints of one slice's triangles
-      if (ns > 1) {
-        rc = chan_workspace(p, (size_t)ns * (size_t)part, s);
-        if (rc != XENG_OK) return rc;
-      }
+      const int ns = std::min(sc.n, std::max(1, (int)(p->ws_bytes / (part * sizeof(int32_t)))));
+      const int sl = ns == sc.n ? sc.len : ((len + ns - 1) / ns + kChunk - 1) / kChunk * kChunk;
       xeng::ChanArgs c;
       c.samples = samples;
       c.vis = vis;
@@ -707,22 +756,21 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       c.F = F;
       c.t0 = t0;
       c.t1 = t1;
-      c.nslices = ns;
+      c.nslices = (len + sl - 1) / sl;
       c.slice_len = sl;
       c.row_stride = (long long)F * N;
       c.t_frame = T;
       // one slice writes vis itself; several store their own triangles into
       // the workspace, and a second kernel sums them into vis
-      c.partial = ns > 1 ? p->d_chan_ws : nullptr;
+      c.partial = ns > 1 ? reinterpret_cast<int32_t*>(p->d_ws) : nullptr;
       c.write_mode = (ns == 1 && add) ? xeng::WM_ADD : xeng::WM_STORE;
-      hipError_t e = xeng::launch_chan(c, fast, s);
+      hipError_t e = small ? xeng::launch_small(c, fast, s) : xeng::launch_chan(c, fast, s);
       if (e != hipSuccess) return hip_fail(p, e, "channel kernel launch");
       if (ns > 1) {
-        e = xeng::launch_chan_reduce(p->d_chan_ws, vis, part, ns, add, s);
+        e = xeng::launch_chan_reduce(c.partial, vis, part, c.nslices, add, s);
         if (e != hipSuccess) return hip_fail(p, e, "slice sum launch");
-        e = hipEventRecord(p->chan_ws_used, s);
-        if (e != hipSuccess) return hip_fail(p, e, "hipEventRecord");
-        p->chan_ws_pending = true;
+        rc = workspace_used(p, s);
+        if (rc != XENG_OK) return rc;
       }
       continue;
     }
@@ -1471,10 +1519,8 @@ int xeng_destroy(xeng_plan_t p) {
   if (p->d_seg_delay) (void)hipFree(p->d_seg_delay);
   if (p->d_blk_delay) (void)hipFree(p->d_blk_delay);
   if (p->d_shifted) (void)hipFree(p->d_shifted);
-  if (p->d_chan_ws) (void)hipFree(p->d_chan_ws);
-  if (p->chan_ws_used) (void)hipEventDestroy(p->chan_ws_used);
-  if (p->d_packed) (void)hipFree(p->d_packed);
-  if (p->packed_used) (void)hipEventDestroy(p->packed_used);
+  if (p->d_ws) (void)hipFree(p->d_ws);
+  if (p->ws_used) (void)hipEventDestroy(p->ws_used);
   if (p->d_fU) (void)hipFree(p->d_fU);
   if (p->d_fX) (void)hipFree(p->d_fX);
   if (p->d_fint) (void)hipFree(p->d_fint);

@@ -26,6 +26,11 @@ struct ChanArgs {
 // fast: F N <= 2^25 (the offsets of 64 rows fit 31 bits)
 hipError_t launch_chan(const ChanArgs& a, bool fast, hipStream_t stream);
 
+// The small-array kernel (N <= 128, xcorr_small.hip): the same arguments; every
+// workgroup covers 128 / small_columns(N) consecutive channels.
+int small_columns(int N);
+hipError_t launch_small(const ChanArgs& a, bool fast, hipStream_t stream);
+
 // vis[i] (+)= sum over s < ns of partial[s n + i], i < n (add: accumulate)
 hipError_t launch_chan_reduce(const int32_t* partial, int32_t* vis, long long n, int ns, bool add,
                               hipStream_t stream);

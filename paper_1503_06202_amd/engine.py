@@ -32,24 +32,32 @@ def vis_shape(N: int, F: int) -> Tuple[int, int, int]:
     return (F, num_baselines(N), 2)
 
 
+# The current stream's handle without building a torch.cuda.Stream (3 us, as
+# much as queueing a kernel; a small frame's call is bound by the host)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _raw_stream is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check_samples(samples: torch.Tensor) -> Tuple[int, int, int]:
-    if samples.dtype != torch.uint8 or samples.dim() != 3:
+    shape = samples.shape
+    if samples.dtype is not torch.uint8 or len(shape) != 3:
         raise ValueError("samples must be a uint8 tensor [T][F][N]")
     if not samples.is_cuda:
         raise ValueError("samples must be on the GPU")
     if not samples.is_contiguous():
         raise ValueError("samples must be contiguous")
-    T, F, N = samples.shape
-    return int(T), int(F), int(N)
+    return shape[0], shape[1], shape[2]
 
 
 def _check_vis(vis: torch.Tensor, N: int, F: int, device) -> None:
-    if vis.dtype != torch.int32 or tuple(vis.shape) != vis_shape(N, F):
+    if vis.dtype is not torch.int32 or vis.shape != vis_shape(N, F):
         raise ValueError(f"vis must be int32 {vis_shape(N, F)}")
     if not vis.is_cuda or not vis.is_contiguous() or vis.device != device:
         raise ValueError("vis must be a contiguous tensor on the samples' GPU")
@@ -103,7 +111,9 @@ class Plan:
 
     def set_tuning(self, split_t: int = 0, kernel: int = 0) -> None:
         """split_t: time slices per tile (0 = automatic); kernel: 0 automatic
-        (above 640 inputs, large frames are repacked into FP6 operands), 1 = 128 x 128 tiles, 2 = 128 x 256 tiles (needs N % 16 == 0), 3 / 4 =
+        (up to 128 inputs the small-array kernel, up to 256 the channel kernel,
+        above 640 large frames are repacked into FP6 operands, else 1), 1 =
+        128 x 128 tiles, 2 = 128 x 256 tiles (needs N % 16 == 0), 3 / 4 =
         128 x 128 tiles with split / common wave roles in diagonal tiles, 5 =
         the channel kernel (one workgroup per channel and time slice; int8,
         N <= 256; other plans use 1)."""

@@ -3,8 +3,8 @@ per instance shape of a batched plan.
 
 Plain form (``tune_plain``): for one frame shape (N, F, T) the tuner times
 every kernel shape the library has on seeded synthetic frames of that shape:
-the automatic choice (kernel 0: the packed path on large frames of more than
-640 inputs), the channel kernel (kernel 5 of ``xeng_plan_set_tuning``; int8, N <= 256),
+the automatic choice (kernel 0: the small-array kernel up to 128 inputs, the
+packed path on large frames of more than 640), the channel kernel (kernel 5 of ``xeng_plan_set_tuning``; int8, N <= 256),
 128 x 128 tiles with split or common wave roles in diagonal tiles (kernel 3
 or 4) and 128 x 256 tiles (kernel 2), each with the automatic time slices and
 with 1, 2 and 4 slices.  It rejects any
