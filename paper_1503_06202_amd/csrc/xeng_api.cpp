@@ -1167,6 +1167,8 @@ int xeng_beamform(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, in
   if (!p || !samples || !beams || N < 1 || F < 1 || T < 1) return XENG_EINVAL;
   if (p->kind != PLAN_SINGLE || p->B < 1 || !p->beams_ready) return XENG_EPLAN;
   if (N != p->N || F != p->F || T > p->T_max) return XENG_EPLAN;
+  const int rc = ensure_cu_count(p);
+  if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const long long row = (long long)F * N;
   const long long seg = beam_segment(row);  // >= 1 by the plan's check
@@ -1183,10 +1185,14 @@ int xeng_beamform(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, in
     a.B = p->B;
     a.S = p->beam_S;
     a.NBT = p->beam_nbt;
+    a.cus = p->cu_count;
     a.tblocks = 0;
-    for (int c0 = 0; c0 < p->beam_nbt; c0 += 4) {
+    // every launch reads the samples: as few as can be, of about equal tiles
+    const int launches = (p->beam_nbt + xeng::kBeamTiles - 1) / xeng::kBeamTiles;
+    for (int k = 0, c0 = 0, nb; k < launches; ++k, c0 += nb) {
+      nb = (p->beam_nbt - c0 + launches - k - 1) / (launches - k);
       a.c0 = c0;
-      const hipError_t e = xeng::launch_beams(a, std::min(4, p->beam_nbt - c0), aligned, s);
+      const hipError_t e = xeng::launch_beams(a, nb, aligned, s);
       if (e != hipSuccess) return hip_fail(p, e, "beamform kernel launch");
     }
   }

@@ -132,13 +132,13 @@ struct BeamArgs {
   int S;                   // steps of 128 inputs: ceil(N / 128)
   int NBT;                 // component tiles in all: ceil(2B / 32)
   int c0;                  // first component tile of this launch
+  int cus;                 // compute units of the device
   int tblocks;             // set by launch_beams
 };
 
-// Rows of one workgroup for nb component tiles per launch (at most 256).
-int beam_rows_per_block(int nb, bool aligned);
-// nb = 1..4 component tiles; aligned: N % 16 == 0 and samples 16-byte
-// aligned.  The host keeps (T + rows per workgroup) F N below 2^31.
+constexpr int kBeamTiles = 6;  // most component tiles of one launch
+// nb = 1..kBeamTiles component tiles; aligned: N % 16 == 0 and samples 16-byte
+// aligned.  The host keeps (T + rows per workgroup, at most 512) F N below 2^31.
 hipError_t launch_beams(BeamArgs a, int nb, bool aligned, hipStream_t stream);
 
 // One work item of the batched persistent kernel.
