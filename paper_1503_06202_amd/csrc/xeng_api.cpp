@@ -518,6 +518,11 @@ static PackedSchedule packed_schedule(long long W, int plen, int sumb, int cus, 
 //   N = 768,  F = 1, T = 32768 (688,000) 79 / 71    T = 8192 (172,000)   45 / 50
 // and short integrations are bound by the visibilities, not the products:
 //   N = 2048, F = 16, T = 512  102 / 128    T = 2048  274 / 240
+//   N = 1776, F = 14, T = 1984 (1470 tiles, FP8)  155 / 163   T = 3072  222 / 217
+//   N = 768,  F = 32, T = 1984 (672 tiles)         86 / 101   T = 2560  141 / 124
+//   N = 1024, F = 16, T = 1536 (576 tiles)         65 / 53
+// so below 2560 samples it is taken from 1024 inputs on where the last wave of
+// tiles (512 workgroups run at a time) leaves a tenth of the slots or more unused.
 // Delays that differ inside a block of 128 inputs (shift_copy) cost the tile
 // kernels a copy of the frame that fetches every line eight times (1.39 ms a
 // GiB), and the packed path only a longer packing pass (0.93 ms): there it
@@ -525,8 +530,9 @@ static PackedSchedule packed_schedule(long long W, int plen, int sumb, int cus, 
 //   N = 128, F = 16, T = 32768  131 / 110    N = 384, F = 64, T = 4096   259 / 130
 //   N = 512, F = 4,  T = 8192 (328,000)  80 / 64    N = 512, F = 1, T = 32768 (328,000)  76 / 81
 static bool packed_pays(int N, int F, int T, bool shift_copy) {
-  const long long work = tiles_per_channel(N) * F * (long long)T;
-  if (T < 1536) return false;
+  const long long tiles = tiles_per_channel(N) * F, work = tiles * T;
+  const bool odd_wave = N >= 1024 && (tiles + 511) / 512 * 512 * 10 >= tiles * 11;
+  if (T < (shift_copy || odd_wave ? 1536 : 2560)) return false;
   return shift_copy ? N >= 128 && work >= 340000 : N > 640 && work >= 230000;
 }
 
