@@ -67,6 +67,10 @@ struct xeng_plan_s {
   std::vector<const void*> uploaded;  // pointers now in d_insts
   hipGraphExec_t graph_exec = nullptr;
   hipStream_t capture_stream = nullptr;
+  // instances that calls take by the packed path, and a plan of the others
+  // (or nullptr, if there are none)
+  std::vector<int> large;
+  xeng_plan_t rest = nullptr;
 
   // output gating (xeng_plan_gated): run tables, pinned staging and device
   int G_max = 0;
@@ -557,13 +561,18 @@ static int packed_sumb(int blocks, int nchan, int plen, int cus) {
 // Correlate by the packed path: per segment of at most XENG_F8_FLUSH_MAX
 // samples and group of channels that fits the workspace, pack the samples and
 // correlate the packed operands.
-static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
-                            int32_t* vis, hipStream_t s) {
+// Workspace of a packed call: channels per group, operands and partial blocks
+// (the largest schedule of the call).
+struct PackedNeed {
+  int group;
+  size_t operands, part;
+};
+
+static PackedNeed packed_need(xeng_plan_t p, int N, int F, int T) {
   const int blocks = (N + kTile - 1) / kTile, tpc = xeng::packed_tiles(blocks);
   const int seg = XENG_F8_FLUSH_MAX, seg_len = std::min(T, seg);
   const size_t per_chan = packed_channel_bytes(N, seg_len);
   const int group = (int)std::max<size_t>(1, std::min<size_t>(F, kPackedMax / per_chan));
-  // partial blocks: the largest schedule of the call
   size_t part = 0;
   for (int k = 0; k < 4; ++k) {
     const int len = k & 1 ? T % seg : seg_len, nch = k & 2 ? F % group : group;
@@ -576,10 +585,17 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
                                           : ((long long)tpc * nch - c.head) * c.tail_slices;
     part = std::max(part, (size_t)items * xeng::PK_PART * sizeof(int2));
   }
-  hipError_t e = hipSuccess;
-  const size_t operands = (per_chan * group + 255) / 256 * 256, need = operands + part;
-  int rc = workspace(p, need, s);
+  return PackedNeed{group, (per_chan * group + 255) / 256 * 256, part};
+}
+
+static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
+                            int32_t* vis, hipStream_t s) {
+  const int blocks = (N + kTile - 1) / kTile, tpc = xeng::packed_tiles(blocks);
+  const int seg = XENG_F8_FLUSH_MAX;
+  const auto [group, operands, part] = packed_need(p, N, F, T);
+  int rc = workspace(p, operands + part, s);
   if (rc != XENG_OK) return rc;
+  hipError_t e = hipSuccess;
   const long long row = (long long)F * N, NB2 = (long long)N * (N + 1);
   const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0);
   for (int t0 = 0; t0 < T; t0 += seg) {
@@ -1205,6 +1221,21 @@ int xeng_beamform(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, in
   return mark_tables(p, s);
 }
 
+// Instances of a batch that run by the packed path, one after another, while
+// the persistent kernel takes the others.  In a batch the tiles of all frames
+// share the chip, so that a frame has to fill it alone to gain from the packed
+// path, unless all of them leave workgroups idle; microseconds, tiles (best of
+// 1, 2 and 4 slices) / packed, by 128 x 128 tiles x samples of an instance:
+//   4 x (2048, 4, 16384)  8.9 M  1579 / 1168    8 x (1024, 4, 16384)  2.4 M  854 / 949
+//   8 x (1024, 4, 32768)  4.7 M  1679 / 1631    6 x (2048, 2, 8192)   2.2 M  614 / 647
+//   2 x (1024, 4, 16384)  2.4 M   262 / 237     2 x (1024, 2, 16384)  1.2 M  183 / 142
+// A named slice count keeps the tiles.
+static bool batch_packs(const xeng_instance& d, long long batch_tiles, int slots) {
+  const long long work = tiles_per_channel(d.N) * d.F * (long long)d.T;
+  return d.split_t == 0 && packed_pays(d.N, d.F, d.T, false) &&
+         work >= (batch_tiles > slots ? 4000000 : 1100000);
+}
+
 int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, unsigned flags) {
   if (!out) return XENG_EINVAL;
   *out = nullptr;
@@ -1277,6 +1308,30 @@ int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, uns
   if (p->items.size() > 0x7fffffffu) {
     delete p;
     return XENG_EINVAL;
+  }
+  if (!shared) {
+    try {
+      // a vis shared between instances takes atomic adds: tiles
+      std::vector<xeng_instance> others;
+      long long tiles = 0;
+      for (int k = 0; k < count; ++k) tiles += descs[k].F * tiles_per_channel(descs[k].N);
+      for (int k = 0; k < count; ++k) {
+        if (batch_packs(descs[k], tiles, cu_count_hint() * kOccupancy))
+          p->large.push_back(k);
+        else
+          others.push_back(descs[k]);
+      }
+      if (!p->large.empty() && !others.empty()) {
+        const int rc = xeng_plan_batch(&p->rest, others.data(), (int)others.size(), flags);
+        if (rc != XENG_OK) {
+          xeng_destroy(p);
+          return rc;
+        }
+      }
+    } catch (const std::bad_alloc&) {
+      xeng_destroy(p);
+      return XENG_ENOMEM;
+    }
   }
   *out = p;
   return XENG_OK;
@@ -1361,10 +1416,66 @@ static int batch_grid(xeng_plan_t p) {
   return (int)std::max(1LL, g);
 }
 
+// A batch with instances for the packed path: those one by one, the others by
+// their own plan.  *done stays false if the call has to take the persistent
+// kernel for all: under capture (see stream_captures), or without the memory.
+static int batch_packed(xeng_plan_t p, const uint8_t* const* samples, int32_t* const* vis,
+                        void* stream, bool graph, bool* done) {
+  *done = false;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (p->large.empty() || stream_captures(s)) return XENG_OK;
+  int rc = ensure_cu_count(p);
+  if (rc != XENG_OK) return rc;
+  size_t need = 0;
+  for (int k : p->large) {
+    if (!samples[k]) continue;
+    const xeng_instance& d = p->insts[k];
+    const PackedNeed n = packed_need(p, d.N, d.F, d.T);
+    need = std::max(need, n.operands + n.part);
+  }
+  if (need) {
+    rc = workspace(p, need, s);
+    if (rc != XENG_OK) return rc == XENG_ENOMEM ? XENG_OK : rc;
+  }
+  if (p->rest) {
+    std::vector<const uint8_t*> x;
+    std::vector<int32_t*> v;
+    try {
+      for (size_t k = 0, l = 0; k < p->insts.size(); ++k) {
+        if (l < p->large.size() && p->large[l] == (int)k) {
+          ++l;
+          continue;
+        }
+        x.push_back(samples[k]);
+        v.push_back(vis[k]);
+      }
+    } catch (const std::bad_alloc&) {
+      return XENG_ENOMEM;
+    }
+    rc = graph ? xeng_correlate_batch_graph(p->rest, x.data(), v.data(), stream)
+               : xeng_correlate_batch(p->rest, x.data(), v.data(), stream);
+    if (rc != XENG_OK) {
+      p->err = p->rest->err;
+      return rc;
+    }
+  }
+  for (int k : p->large) {
+    if (!samples[k]) continue;
+    const xeng_instance& d = p->insts[k];
+    rc = correlate_packed(p, samples[k], d.N, d.F, d.T, vis[k], s);
+    if (rc != XENG_OK) return rc;
+  }
+  *done = true;
+  return XENG_OK;
+}
+
 int xeng_correlate_batch(xeng_plan_t p, const uint8_t* const* samples, int32_t* const* vis,
                          void* stream) {
   int rc = batch_check(p, samples, vis);
   if (rc != XENG_OK) return rc;
+  bool done = false;
+  rc = batch_packed(p, samples, vis, stream, false, &done);
+  if (rc != XENG_OK || done) return rc;
   rc = batch_setup(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1381,6 +1492,9 @@ int xeng_correlate_batch_graph(xeng_plan_t p, const uint8_t* const* samples,
                                int32_t* const* vis, void* stream) {
   int rc = batch_check(p, samples, vis);
   if (rc != XENG_OK) return rc;
+  bool done = false;
+  rc = batch_packed(p, samples, vis, stream, true, &done);
+  if (rc != XENG_OK || done) return rc;
   rc = batch_setup(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1513,6 +1627,7 @@ int xeng_correlate_batch_noalloc(const xeng_instance* descs, int count, unsigned
 
 int xeng_destroy(xeng_plan_t p) {
   if (!p) return XENG_OK;
+  if (p->rest) (void)xeng_destroy(p->rest);
   if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
   if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
   for (int r = 0; r < kStageRing; ++r)
