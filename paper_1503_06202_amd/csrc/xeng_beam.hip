@@ -33,8 +33,9 @@
 // second.  Five or six tiles leave registers for one time tile a wave, and one
 // launch that reads the samples once.
 //
-// Output rows (8B bytes) are stored tile by tile within a row, past the caches:
-// with the row's tiles apart in time, lines left L2 in pieces.
+// Output rows (8B bytes) are stored tile by tile within a row, past the caches
+// where rows are whole sectors: with the row's tiles apart in time, lines left
+// L2 in pieces.
 //
 // Measured, us, before -> after (bytes at 5.0 TB/s):
 //   N = 2048, F = 16, T = 32768   B = 16 236 -> 229 (228), B = 64 500 -> 366
@@ -43,6 +44,8 @@
 //   N = 1090, F = 8, T = 20011, B = 20    375 -> 81 (40), byte loads before
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "xcorr_tile.hpp"
 #include "xeng_internal.hpp"
@@ -179,18 +182,34 @@ __global__ void __launch_bounds__(64 * NW) beam_kernel(BeamArgs a) {
 #pragma unroll
   for (int c = 0; c < NB; ++c) corr[c] = a.corr[((long long)f * a.NBT + a.c0 + c) * 32 + r];
   int32_t* const out = a.beams + (long long)f * ncomp + 32 * a.c0 + r;
+  auto write = [&](auto past_caches) {
 #pragma unroll
-  for (int j = 0; j < TT; ++j)
+    for (int j = 0; j < TT; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int t = tbase + 32 * j + 8 * (v >> 2) + 4 * h + (v & 3);
-      if (t < a.T) {
+      for (int v = 0; v < 16; ++v) {
+        const int t = tbase + 32 * j + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (t < a.T) {
 #pragma unroll
-        for (int c = 0; c < NB; ++c)
-          if (32 * (a.c0 + c) + r < ncomp)
-            __builtin_nontemporal_store(acc[j][c][v] - corr[c], out + (long long)t * out_row + 32 * c);
+          for (int c = 0; c < NB; ++c)
+            if (32 * (a.c0 + c) + r < ncomp) {
+              int32_t* const o = out + (long long)t * out_row + 32 * c;
+              if constexpr (decltype(past_caches)::value)
+                __builtin_nontemporal_store(acc[j][c][v] - corr[c], o);
+              else
+                *o = acc[j][c][v] - corr[c];
+            }
+        }
       }
-    }
+  };
+  // Past the caches if rows are whole 64-byte sectors (N = 64, F = 64, T =
+  // 16384, B = 40: 91 us against 143 through them); other rows share sectors
+  // with the next channel's, which L2 has to join (B = 45: 203 against 153) unless
+  // the samples are most of the traffic (N = 1264, F = 5, T = 35072, B = 45: 81
+  // against 92).
+  if (a.B % 8 == 0 || 24 * a.B <= a.N)
+    write(std::true_type{});
+  else
+    write(std::false_type{});
 }
 
 template <int NB, int TT, int NW, bool ALIGNED>
@@ -205,18 +224,20 @@ hipError_t launch_nb(BeamArgs a, hipStream_t stream) {
 }
 
 // Time tiles and waves: registers hold TT x NB accumulators and two steps of
-// samples.  Three or four tiles take 512 rows per workgroup once that leaves no
-// CU idle and there are several steps (N = 2048, F = 16, T = 32768, B = 64: 366
-// us against 468 with 128 rows; but N = 864, F = 3, T = 20864, B = 48, 123
-// workgroups: 31 against 24, and N = 64, F = 64, T = 16384, B = 40, whose time is
-// the output's: 109 against 93).  Unaligned rows with one or two tiles take one
+// samples.  Three or four tiles take 512 rows per workgroup (one a CU) if the
+// last round of workgroups leaves few CUs idle and there are several steps (N =
+// 2048, F = 16, T = 32768, B = 64, four rounds: 366 us against 468 with 128 rows;
+// but N = 1264, F = 5, T = 35072, B = 45, 345 workgroups: 120 against 111; N =
+// 864, F = 3, T = 20864, B = 48, 123 workgroups: 31 against 24; and N = 64, F =
+// 64, T = 16384, B = 40, whose time is the output's: 109 against 93).  Unaligned rows with one or two tiles take one
 // time tile (N = 1090, F = 8, T = 20011, B = 20: 81 against 101 with two).
 template <int NB, bool ALIGNED>
 hipError_t launch_rows(const BeamArgs& a, hipStream_t stream) {
   if constexpr (NB > 4) {
     return launch_nb<NB, 1, 8, ALIGNED>(a, stream);
   } else if constexpr (NB > 2) {
-    if (a.S > 1 && (long long)a.F * ((a.T + 511) / 512) >= a.cus)
+    const long long grid = (long long)a.F * ((a.T + 511) / 512);
+    if (a.S > 1 && (grid + a.cus - 1) / a.cus * a.cus * 5 <= grid * 6)
       return launch_nb<NB, 2, 8, ALIGNED>(a, stream);
     return launch_nb<NB, 1, 4, ALIGNED>(a, stream);
   } else {
