@@ -453,6 +453,24 @@ __device__ __forceinline__ void put_pairs(int32_t* base, const int (&b)[K], cons
   }
 }
 
+// put_pairs in WM_ADD with all reads before the first store: one by one, each
+// pair waits for its own read (accumulating, tiles: N = 1808, F = 4, T = 448
+// 44.9 -> 31.2 us; packed: N = 2048, F = 4, T = 32768 614 -> 571).  A pair that is
+// not in ok reads pair 0.  The channel kernel adds one by one: reads ahead spill
+// in its chunk loop (N = 256, F = 64, T = 32768: 217 us, 220 so).
+template <int K>
+__device__ __forceinline__ void add_pairs(int32_t* base, const int (&b)[K], const int (&vr)[K],
+                                          const int (&vi)[K], uint32_t ok) {
+  int2 old[K];
+#pragma unroll
+  for (int v = 0; v < K; ++v)
+    old[v] = *reinterpret_cast<const int2*>(base + 2 * ((ok & (1u << v)) ? b[v] : 0));
+#pragma unroll
+  for (int v = 0; v < K; ++v)
+    if (ok & (1u << v))
+      *reinterpret_cast<int2*>(base + 2 * b[v]) = make_int2(old[v].x + vr[v], old[v].y + vi[v]);
+}
+
 // The mode a work item writes in: its int32 atomic adds become one 64-bit
 // atomic per baseline where vis is 8-byte aligned (every channel's and gate's
 // triangle then is).
@@ -497,7 +515,10 @@ __device__ __forceinline__ void write_blocks_m(int32_t* base, int N, int rs0, in
         vr[u] = to_i32(re[ai][bi][v]) + ci.x + cj.x;
         vi[u] = (i == j) ? 0 : to_i32(im[ai][bi][v]) + ci.y + cj.y;
       }
-      put_pairs<MODE>(base, b, vr, vi, ok);
+      if constexpr (MODE == WM_ADD)
+        add_pairs(base, b, vr, vi, ok);
+      else
+        put_pairs<MODE>(base, b, vr, vi, ok);
     }
   }
 }
@@ -517,8 +538,12 @@ __device__ __forceinline__ void write_blocks(int32_t* vis, int N, long long NB, 
     write_blocks_m<WM_ATOMIC64>(base, N, rs0, cs0, lr0, lc0, corr, lane, mask, re, im);
     return;
   }
-  // stores, read-add-stores and 32-bit atomics one baseline at a time (the
-  // fewest live registers: the chunk loop keeps its allocation)
+  if (mode == WM_ADD) {
+    write_blocks_m<WM_ADD>(base, N, rs0, cs0, lr0, lc0, corr, lane, mask, re, im);
+    return;
+  }
+  // stores and 32-bit atomics one baseline at a time (the fewest live registers:
+  // the chunk loop keeps its allocation)
 #pragma unroll
   for (int ab = 0; ab < 4; ++ab) {
     const int ai = ab >> 1, bi = ab & 1;
@@ -536,9 +561,6 @@ __device__ __forceinline__ void write_blocks(int32_t* vis, int N, long long NB, 
         const int vi = (i == j) ? 0 : to_i32(im[ai][bi][v]) + ci.y + cj.y;
         if (mode == WM_STORE) {
           *reinterpret_cast<int2*>(p) = make_int2(vr, vi);
-        } else if (mode == WM_ADD) {
-          int2 o = *reinterpret_cast<int2*>(p);
-          *reinterpret_cast<int2*>(p) = make_int2(o.x + vr, o.y + vi);
         } else {
           atomicAdd(p, vr);
           if (vi) atomicAdd(p + 1, vi);

@@ -118,19 +118,29 @@ __device__ __forceinline__ void put16(const TileOut& o, int blk, int i0, int j0,
     return;
   }
   const int j = j0 + (lane & 31);
+  if (o.mode == WM_ADD) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {  // eight at a time: fewer live registers
+      int b[8], r[8], m[8];
+      uint32_t ok = 0u;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int i = i0 + blk_row16(8 * h + u, lane);
+        ok |= (uint32_t)(i < o.N && j < o.N && j >= i) << u;
+        b[u] = pair_index(i, j, o.N);
+        r[u] = vr[8 * h + u];
+        m[u] = i == j ? 0 : vi[8 * h + u];
+      }
+      add_pairs(o.base, b, r, m, ok);
+    }
+    return;
+  }
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int i = i0 + blk_row16(v, lane);
-    if (i < o.N && j < o.N && j >= i) {
-      int2* q = reinterpret_cast<int2*>(o.base + 2 * pair_index(i, j, o.N));
-      int2 r = make_int2(vr[v], i == j ? 0 : vi[v]);
-      if (o.mode == WM_ADD) {
-        const int2 w = *q;
-        r.x += w.x;
-        r.y += w.y;
-      }
-      *q = r;
-    }
+    if (i < o.N && j < o.N && j >= i)
+      *reinterpret_cast<int2*>(o.base + 2 * pair_index(i, j, o.N)) =
+          make_int2(vr[v], i == j ? 0 : vi[v]);
   }
 }
 
