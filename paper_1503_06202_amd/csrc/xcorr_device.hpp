@@ -75,10 +75,10 @@ __device__ __forceinline__ void load_pieces_fast(v4i (&raw)[4], const uint8_t* _
 // 16-byte load at any alignment (sixteen byte loads, as rows of N % 16 != 0
 // inputs took before, cost 3 to 8 times the frame's whole time: 1927 us against
 // 230 us on N = 250, F = 64, T = 32768): what it reads past input N is the
-// next channel or row, and those inputs' baselines are never written.  Only where
-// the load would pass the frame's end are the bytes read one by one, with
-// absent inputs as the code of 0 + 0i: in row t_fast (the frame's last row, in
-// its last channel, if N is not a multiple of 16; see fast_rows).
+// next channels or rows, and those inputs' baselines are never written.  Only
+// where the load could pass the frame's end are the bytes read one by one, with
+// absent inputs as the code of 0 + 0i: a row's last piece from row t_fast on
+// (see fast_rows).
 __device__ __forceinline__ v4i load_piece_edge(const uint8_t* __restrict__ samples,
                                                long long row_stride, int f, int N, int n_first,
                                                int t, int t_end, int t_fast, int d = 0) {

@@ -13,11 +13,20 @@ namespace xeng {
 // 32-bit ones (see put_pairs in xcorr_device.hpp).
 enum WriteMode { WM_STORE = 0, WM_ADD = 1, WM_ATOMIC = 2, WM_ATOMIC64 = 3 };
 
-// Rows of a T-row frame whose 16-byte pieces may all be read in channel f of F:
-// the last piece of a row of N inputs may reach into the next channel or row,
-// which the frame's very last row does not have.
+// Rows t < fast_rows(T, N, f, F) of channel f are those whose 16-byte pieces
+// (inputs 0, 16, .. below N) all end inside the frame [T][F][N].  A channel's last
+// piece reads on past input N, into the following channels or rows: past the
+// frame's last byte in its last row, of the last channel from 8 inputs on, and
+// below that also of channels and (F N < 16) in rows before it.  No larger
+// count would do; it falls with f, and may be negative (rows of the history
+// before the frame are counted below 0).
 __host__ __device__ inline int fast_rows(int T, int N, int f, int F) {
-  return T - ((N & 15) && f == F - 1 ? 1 : 0);
+  // bytes that row T - 1 of the channel reads past the frame, at most 15
+  const long long over = (N + 15) / 16 * 16 - (long long)(F - f) * N;
+  if (over <= 0) return T;
+  const long long all = (long long)F * N;
+  const int row = all < 16 ? (int)all : 16;  // bytes a row, as far as they matter
+  return T - ((int)over + row - 1) / row;
 }
 
 // Arguments of the tile kernel: one frame, all channels.
