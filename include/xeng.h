@@ -26,8 +26,10 @@
  * Execution: every compute entry point is asynchronous and ordered on the
  * caller's HIP stream (a hipStream_t passed as void*; NULL is the null
  * stream).  No host synchronisation and no host allocation happen on the call
- * path of xeng_correlate.  A plan is not re-entrant: at most one call in flight
- * per plan; distinct plans are independent.
+ * path of xeng_correlate, but for a call that needs more plan-owned device
+ * memory than the plan has: it allocates, and first waits for the plan's last
+ * call that used the memory it replaces.  A plan is not re-entrant: at most one
+ * call in flight per plan; distinct plans are independent.
  *
  * Errors: functions return XENG_OK (0) or a negative code; nothing throws
  * across the ABI.  XENG_EINVAL, XENG_EPLAN and XENG_EOVERFLOW are decided on
@@ -122,7 +124,9 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * GiB of operands (or one channel's), larger frames run in groups of channels.
  * A call under HIP graph capture that needs any of this memory, or one for
  * which it cannot be allocated, takes the tile kernels.  Calls of one plan on
- * several streams take turns with that memory: the library orders them.
+ * several streams (hipStreamPerThread of several threads included) take turns
+ * with that memory: the library orders them, on the device.  A stream may be
+ * destroyed while the plan lives.
  * Errors: XENG_EINVAL (NULL plan or pointer, T < 1), XENG_EPLAN (N or F differ
  * from the plan, T > T_max), XENG_EOVERFLOW (T > XENG_T_EXACT_MAX),
  * XENG_ENOMEM (that memory cannot be allocated), XENG_EHIP.
@@ -249,7 +253,7 @@ int xeng_plan_set_delays(xeng_plan_t p, const int32_t *delays, int D_max);
  *            set = sample (t, f, i) invalid; bits of inputs >= N are ignored.
  *   vis      as xeng_correlate; counts as above (both overwritten, or added to
  *            with XENG_ACCUMULATE).
- * Asynchronous on `stream`, with no host synchronisation.  Rows with one
+ * Asynchronous on `stream`, as xeng_correlate.  Rows with one
  * invalid input are counted per input; rows with several become rows of an
  * event frame, which the int8 MFMA kernel correlates: identical rows within a
  * block of 64 (a saturated input, a lost packet) take one or two event rows,

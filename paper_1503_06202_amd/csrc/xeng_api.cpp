@@ -92,8 +92,7 @@ struct xeng_plan_s {
   uint8_t* d_ws = nullptr;
   size_t ws_bytes = 0;
   bool ws_pending = false;        // a call has used it
-  hipStream_t ws_stream = nullptr;  // the stream of those calls, until a second one appears
-  hipEvent_t ws_used = nullptr;   // from then on: recorded after every use
+  hipEvent_t ws_used = nullptr;   // recorded after every use; NULL while all were on the null stream
 
   // time shifting (xeng_plan_set_delays): per-segment delays and block maxima
   bool shift = false;
@@ -390,27 +389,49 @@ int xeng_plan_set_tuning(xeng_plan_t p, int split_t, int kernel) {
 
 const char* xeng_plan_error(xeng_plan_t p) { return p ? p->err.c_str() : ""; }
 
+// Whether `s` is being captured into a HIP graph (or cannot be asked): such a
+// call takes the kernels that need no plan-owned workspace, which a later call
+// could replace or overwrite between the graph's replays.
+static bool stream_captures(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// Record the workspace's event on `s`.
+static int workspace_record(xeng_plan_t p, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (!p->ws_used) e = hipEventCreateWithFlags(&p->ws_used, hipEventDisableTiming);
+  if (e != hipSuccess) return hip_fail(p, e, "hipEventCreate");
+  e = hipEventRecord(p->ws_used, s);
+  return e == hipSuccess ? XENG_OK : hip_fail(p, e, "hipEventRecord");
+}
+
 // The plan's workspace, at least `bytes`, for a call on `s`: grown when needed
-// (after the plan's calls have finished), and ordered after the last call that
-// used it.  Calls on one stream are in order anyway, and an event recorded
-// after each of them costs more than a small frame (12.2 us a call with, 7.4
-// without, 16 inputs and 256 samples in two slices).  So a plan records none
-// until a call arrives on a second stream; that call waits once, on the host,
-// for the device, and from then on every use records an event that the next
-// one waits for on its stream.
+// (after the plan's last call that used it), and ordered after that call.
+// Every use records an event that the next one waits for on its stream, except
+// while all uses are on the null stream, which orders them itself and is never
+// destroyed: an event costs more than a small frame (12.2 us a call with, 7.4
+// without, 16 inputs and 256 samples in two slices).  The first use on another
+// stream records the event for those before it.  An equal handle says nothing
+// on other streams: hipStreamPerThread is another one in every thread, and a
+// destroyed stream's handle may be given out again while its work still runs.
+// XENG_ENOMEM: the call has to do without (no memory, or its order after the
+// null stream cannot be had while another stream's capture includes that one).
 static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
   hipError_t e = hipSuccess;
-  if (p->ws_pending && !p->ws_used && s != p->ws_stream) {
-    e = hipDeviceSynchronize();
-    if (e != hipSuccess) return hip_fail(p, e, "hipDeviceSynchronize");
-    e = hipEventCreateWithFlags(&p->ws_used, hipEventDisableTiming);
-    if (e != hipSuccess) return hip_fail(p, e, "hipEventCreate");
-    p->ws_pending = false;
+  if (p->ws_pending && !p->ws_used && s != nullptr) {
+    if (stream_captures(nullptr)) return XENG_ENOMEM;
+    const int rc = workspace_record(p, nullptr);
+    if (rc != XENG_OK) return rc;
   }
   if (bytes > p->ws_bytes) {
     if (p->ws_pending) {
-      e = hipDeviceSynchronize();
-      if (e != hipSuccess) return hip_fail(p, e, "hipDeviceSynchronize");
+      e = p->ws_used ? hipEventSynchronize(p->ws_used) : hipStreamSynchronize(nullptr);
+      if (e != hipSuccess) return hip_fail(p, e, "workspace synchronization");
       p->ws_pending = false;
     }
     if (p->d_ws) (void)hipFree(p->d_ws);
@@ -431,15 +452,11 @@ static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
   return XENG_OK;
 }
 
-// After a call's last kernel that uses the workspace.
+// After the last kernel of a call that may use the workspace, also where a
+// later launch of the call failed.
 static int workspace_used(xeng_plan_t p, hipStream_t s) {
-  if (p->ws_used) {
-    const hipError_t e = hipEventRecord(p->ws_used, s);
-    if (e != hipSuccess) return hip_fail(p, e, "hipEventRecord");
-  }
-  p->ws_stream = s;
   p->ws_pending = true;
-  return XENG_OK;
+  return s != nullptr || p->ws_used ? workspace_record(p, s) : XENG_OK;
 }
 
 // The packed path (xeng_packed.hpp): bytes of one channel's operands and code
@@ -540,27 +557,12 @@ static bool packed_pays(int N, int F, int T, bool shift_copy) {
   return shift_copy ? N >= 128 && work >= 340000 : N > 640 && work >= 230000;
 }
 
-// Whether `s` is being captured into a HIP graph (or cannot be asked): such a
-// call takes the kernels that need no plan-owned workspace, which a later call
-// could replace or overwrite between the graph's replays.
-static bool stream_captures(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return st != hipStreamCaptureStatusNone;
-}
-
 static int packed_sumb(int blocks, int nchan, int plen, int cus) {
   const long long wgs = (long long)blocks * nchan *
                         ((plen + xeng::PK_SUMB_LONG - 1) / xeng::PK_SUMB_LONG);
   return wgs >= 4LL * cus ? xeng::PK_SUMB_LONG : xeng::PK_SUMB_SHORT;
 }
 
-// Correlate by the packed path: per segment of at most XENG_F8_FLUSH_MAX
-// samples and group of channels that fits the workspace, pack the samples and
-// correlate the packed operands.
 // Workspace of a packed call: channels per group, operands and partial blocks
 // (the largest schedule of the call).
 struct PackedNeed {
@@ -588,13 +590,14 @@ static PackedNeed packed_need(xeng_plan_t p, int N, int F, int T) {
   return PackedNeed{group, (per_chan * group + 255) / 256 * 256, part};
 }
 
-static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
-                            int32_t* vis, hipStream_t s) {
+// Queue the packed path: per segment of at most XENG_F8_FLUSH_MAX samples and
+// group of channels that fits the workspace, pack the samples and correlate the
+// packed operands.
+static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8_t* samples, int N,
+                              int F, int T, int32_t* vis, hipStream_t s) {
   const int blocks = (N + kTile - 1) / kTile, tpc = xeng::packed_tiles(blocks);
   const int seg = XENG_F8_FLUSH_MAX;
-  const auto [group, operands, part] = packed_need(p, N, F, T);
-  int rc = workspace(p, operands + part, s);
-  if (rc != XENG_OK) return rc;
+  const auto [group, operands, part] = need;
   hipError_t e = hipSuccess;
   const long long row = (long long)F * N, NB2 = (long long)N * (N + 1);
   const bool aligned = (N % 16 == 0) && ((reinterpret_cast<uintptr_t>(samples) & 15) == 0);
@@ -650,8 +653,18 @@ static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F,
       if (e != hipSuccess) return hip_fail(p, e, "packed correlation launch");
     }
   }
-  rc = workspace_used(p, s);
+  return XENG_OK;
+}
+
+// Correlate by the packed path (XENG_ENOMEM: nothing was queued).
+static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
+                            int32_t* vis, hipStream_t s) {
+  const PackedNeed need = packed_need(p, N, F, T);
+  int rc = workspace(p, need.operands + need.part, s);
   if (rc != XENG_OK) return rc;
+  rc = launch_packed_path(p, need, samples, N, F, T, vis, s);
+  const int used = workspace_used(p, s);
+  if (rc != XENG_OK || used != XENG_OK) return rc != XENG_OK ? rc : used;
   return p->shift ? mark_tables(p, s) : XENG_OK;
 }
 
@@ -787,13 +800,13 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       c.partial = ns > 1 ? reinterpret_cast<int32_t*>(p->d_ws) : nullptr;
       c.write_mode = (ns == 1 && add) ? xeng::WM_ADD : xeng::WM_STORE;
       hipError_t e = small ? xeng::launch_small(c, fast, s) : xeng::launch_chan(c, fast, s);
-      if (e != hipSuccess) return hip_fail(p, e, "channel kernel launch");
-      if (ns > 1) {
+      if (e == hipSuccess && ns > 1)
         e = xeng::launch_chan_reduce(c.partial, vis, part, c.nslices, add, s);
-        if (e != hipSuccess) return hip_fail(p, e, "slice sum launch");
+      if (ns > 1) {
         rc = workspace_used(p, s);
         if (rc != XENG_OK) return rc;
       }
+      if (e != hipSuccess) return hip_fail(p, e, "channel kernel launch");
       continue;
     }
     const long long W = tpc * F;  // tiles of the launch
