@@ -1486,14 +1486,17 @@ int xeng_correlate_batch(xeng_plan_t p, const uint8_t* const* samples, int32_t* 
                          void* stream) {
   int rc = batch_check(p, samples, vis);
   if (rc != XENG_OK) return rc;
-  bool done = false;
-  rc = batch_packed(p, samples, vis, stream, false, &done);
-  if (rc != XENG_OK || done) return rc;
+  // also before calls by the packed path: a later call under capture takes the
+  // persistent kernel for all instances, and can neither allocate its tables nor
+  // have its pointers copied from staging that later calls refill
   rc = batch_setup(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = batch_upload(p, samples, vis, s);
   if (rc != XENG_OK) return rc;
+  bool done = false;
+  rc = batch_packed(p, samples, vis, stream, false, &done);
+  if (rc != XENG_OK || done) return rc;
   hipError_t e = xeng::launch_batch(p->d_insts, (int)p->insts.size(), p->d_items,
                                     (int)p->items.size(), p->d_counter, batch_grid(p), p->form,
                                     p->any_zero, s);
@@ -1505,14 +1508,17 @@ int xeng_correlate_batch_graph(xeng_plan_t p, const uint8_t* const* samples,
                                int32_t* const* vis, void* stream) {
   int rc = batch_check(p, samples, vis);
   if (rc != XENG_OK) return rc;
-  bool done = false;
-  rc = batch_packed(p, samples, vis, stream, true, &done);
-  if (rc != XENG_OK || done) return rc;
-  rc = batch_setup(p);
+  // a graph cannot be launched into a capture: its kernels are captured instead
+  if (stream_captures(static_cast<hipStream_t>(stream)))
+    return xeng_correlate_batch(p, samples, vis, stream);
+  rc = batch_setup(p);  // see xeng_correlate_batch
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = batch_upload(p, samples, vis, s);
   if (rc != XENG_OK) return rc;
+  bool done = false;
+  rc = batch_packed(p, samples, vis, stream, true, &done);
+  if (rc != XENG_OK || done) return rc;
   if (!p->graph_exec) {
     // The kernels read every pointer from the device instance table, so one
     // captured graph serves every set of buffers.

@@ -52,3 +52,37 @@ def test_batch_with_large_frames(insts, form, accumulate):
             assert torch.equal(v, ref[k] + base if k % 2 == 0 else torch.full_like(v, 7))
 
 
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("insts", [FEW, MANY])
+def test_captured_after_a_call_by_the_packed_path(insts, graph):
+    # a program's usual order: one call, then the same call captured; other
+    # eager calls (the same buffers) between the replays
+    x = frames(insts, 9)
+    y = [a.clone() for a in x]
+    ref = [want(i, a) for i, a in zip(insts, x)]
+    other = frames(insts, 10)
+    ref_other = [want(i, a) for i, a in zip(insts, other)]
+    vis = [torch.zeros(vis_shape(N, F), dtype=torch.int32, device=DEV) for N, F, T in insts]
+    print(f"captured batch of {len(insts)} graph={graph}", flush=True)
+    with BatchPlan(insts) as bp:
+        bp.correlate(x, vis, graph=graph)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            bp.correlate(x, vis, graph=graph)
+        for src, want_now in ((y, ref), (other, ref_other), (y, ref)):
+            for a, b in zip(x, src):
+                a.copy_(b)
+            for replayed in (True, False, True):
+                for v in vis:
+                    v.zero_()
+                if replayed:
+                    g.replay()
+                else:
+                    bp.correlate(x, vis, graph=graph)
+                torch.cuda.synchronize()
+                for k, v in enumerate(vis):
+                    assert torch.equal(v, want_now[k]), (k, insts[k], replayed)
+        del g
