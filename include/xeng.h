@@ -125,8 +125,10 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * A call under HIP graph capture that needs any of this memory, or one for
  * which it cannot be allocated, takes the tile kernels.  Calls of one plan on
  * several streams (hipStreamPerThread of several threads included) take turns
- * with that memory: the library orders them, on the device.  A stream may be
- * destroyed while the plan lives.
+ * with that memory: the library orders them, on the device, by events.  Before a
+ * stream is destroyed (hipStreamPerThread: before its thread ends) its calls must
+ * have finished, if the plan is called again on another one: an event does not
+ * outlive its stream.
  * Errors: XENG_EINVAL (NULL plan or pointer, T < 1), XENG_EPLAN (N or F differ
  * from the plan, T > T_max), XENG_EOVERFLOW (T > XENG_T_EXACT_MAX),
  * XENG_ENOMEM (that memory cannot be allocated), XENG_EHIP.

@@ -401,6 +401,19 @@ static bool stream_captures(hipStream_t s) {
   return st != hipStreamCaptureStatusNone;
 }
 
+// While it lives, this thread may allocate, free and wait although another
+// stream is being captured, here or in another thread (a capture in the default
+// mode refuses that to all threads): none of it concerns that capture.
+struct BesideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  BesideCaptures() = default;
+  BesideCaptures(const BesideCaptures&) = delete;
+  ~BesideCaptures() {
+    if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
 // Record the workspace's event on `s`.
 static int workspace_record(xeng_plan_t p, hipStream_t s) {
   hipError_t e = hipSuccess;
@@ -417,8 +430,8 @@ static int workspace_record(xeng_plan_t p, hipStream_t s) {
 // destroyed: an event costs more than a small frame (12.2 us a call with, 7.4
 // without, 16 inputs and 256 samples in two slices).  The first use on another
 // stream records the event for those before it.  An equal handle says nothing
-// on other streams: hipStreamPerThread is another one in every thread, and a
-// destroyed stream's handle may be given out again while its work still runs.
+// on other streams: hipStreamPerThread is another one in every thread, and the
+// handles of destroyed streams are given out again.
 // XENG_ENOMEM: the call has to do without (no memory, or its order after the
 // null stream cannot be had while another stream's capture includes that one).
 static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
@@ -429,6 +442,7 @@ static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
     if (rc != XENG_OK) return rc;
   }
   if (bytes > p->ws_bytes) {
+    const BesideCaptures relaxed;
     if (p->ws_pending) {
       e = p->ws_used ? hipEventSynchronize(p->ws_used) : hipStreamSynchronize(nullptr);
       if (e != hipSuccess) return hip_fail(p, e, "workspace synchronization");

@@ -48,6 +48,8 @@ def test_per_thread_streams_take_turns(N, F, T):
                         assert rc == _lib.XENG_OK, rc
                         turn[0] += 1
                         lock.notify_all()
+                # a thread's stream ends with it, and events of work left there with the stream
+                torch.cuda.ExternalStream(2).synchronize()
             except BaseException as err:  # reported by the main thread
                 with lock:
                     fail.append(err)
@@ -91,3 +93,30 @@ def test_second_stream_does_not_wait_on_the_host(N, F, T, first):
     assert not waited
     for v, k in zip(vis, (0, 1, 0)):
         assert np.array_equal(v.cpu().numpy(), ref[k])
+
+
+@pytest.mark.parametrize("N,F,T", SHAPES)
+def test_first_and_growing_calls_beside_a_capture(N, F, T):
+    # calls on a stream of their own, which allocate, while another is captured
+    x, ref = frames(N, F, T, 1)
+    half = x[0][:T // 2]
+    ref_half = oracle.to_int32(oracle.correlate(half.cpu().numpy()))
+    vis = [torch.zeros(vis_shape(N, F), dtype=torch.int32, device=DEV) for _ in range(3)]
+    a, b, other = torch.ones(64, device=DEV), torch.zeros(64, device=DEV), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    print(f"beside a capture N={N} F={F} T={T}", flush=True)
+    with Plan(N, F, T) as p, Plan(N, F, T) as q:
+        q.correlate(half, vis[2], stream=other)  # its workspace grows below
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            b.add_(a)
+            p.correlate(x[0], vis[0], stream=other)
+            q.correlate(x[0], vis[1], stream=other)
+        for k in range(1, 4):
+            g.replay()
+            torch.cuda.synchronize()
+            assert (b == k).all()
+    assert np.array_equal(vis[0].cpu().numpy(), ref[0])
+    assert np.array_equal(vis[1].cpu().numpy(), ref[0])
+    assert np.array_equal(vis[2].cpu().numpy(), ref_half)
