@@ -201,12 +201,14 @@ __global__ void __launch_bounds__(64 * NW) beam_kernel(BeamArgs a) {
         }
       }
   };
-  // Past the caches if rows are whole 64-byte sectors (N = 64, F = 64, T =
-  // 16384, B = 40: 91 us against 143 through them); other rows share sectors
-  // with the next channel's, which L2 has to join (B = 45: 203 against 153) unless
-  // the samples are most of the traffic (N = 1264, F = 5, T = 35072, B = 45: 81
-  // against 92).
-  if (a.B % 8 == 0 || 24 * a.B <= a.N)
+  // Past the caches if rows are whole 64-byte sectors, microseconds through / past
+  // them: N = 96, F = 8, T = 174762, B = 48 191 / 118; N = 2048, F = 8, T = 8192,
+  // B = 64 47.2 / 45.5.  Other rows share sectors with the next channel's, which
+  // L2 has to join: N = 96, F = 8, T = 174762, B = 1 62 / 71; N = 224, F = 8, T =
+  // 1170, B = 1 10.8 / 12.0; N = 2048, F = 16, T = 32768, B = 3 224 / 237, B = 50
+  // 332 / 364; N = 1728, F = 3, T = 40000, B = 45 57 / 66.  (A few gain all the
+  // same, N = 1264, F = 5, T = 35072, B = 45 91 / 79, by no rule in sight.)
+  if (a.B % 8 == 0)
     write(std::true_type{});
   else
     write(std::false_type{});
