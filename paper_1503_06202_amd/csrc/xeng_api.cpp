@@ -32,6 +32,9 @@ constexpr int kSplitMax = 128;
 // takes more on its own gets what it needs); larger frames run in groups of
 // channels.
 constexpr size_t kPackedMax = 4ull << 30;
+// Calls that do without a workspace after its memory was refused, before one
+// asks again: a refusal costs more than many a frame.
+constexpr int kRefusedCalls = 64;
 constexpr int kStageRing = 4;  // pinned staging copies of a batch plan's instance table
 
 enum PlanKind { PLAN_SINGLE = 1, PLAN_BATCH = 2 };
@@ -91,6 +94,9 @@ struct xeng_plan_s {
   // packed operands): plan-owned, grown on demand; see workspace()
   uint8_t* d_ws = nullptr;
   size_t ws_bytes = 0;
+  // the size last refused for want of memory, asked for again after kRefusedCalls calls
+  size_t ws_refused = SIZE_MAX;
+  int ws_skipped = 0;
   bool ws_pending = false;        // a call has used it
   hipEvent_t ws_used = nullptr;   // recorded after every use; NULL while all were on the null stream
 
@@ -442,23 +448,30 @@ static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
     if (rc != XENG_OK) return rc;
   }
   if (bytes > p->ws_bytes) {
+    if (bytes >= p->ws_refused && ++p->ws_skipped < kRefusedCalls) return XENG_ENOMEM;
     const BesideCaptures relaxed;
+    // the new memory first: a plan that cannot grow keeps what it has
+    uint8_t* grown = nullptr;
+    e = hipMalloc((void**)&grown, bytes);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (e != hipErrorOutOfMemory) return hip_fail(p, e, "hipMalloc (workspace)");
+      p->ws_refused = bytes;
+      p->ws_skipped = 0;
+      return XENG_ENOMEM;
+    }
     if (p->ws_pending) {
       e = p->ws_used ? hipEventSynchronize(p->ws_used) : hipStreamSynchronize(nullptr);
-      if (e != hipSuccess) return hip_fail(p, e, "workspace synchronization");
+      if (e != hipSuccess) {
+        (void)hipFree(grown);
+        return hip_fail(p, e, "workspace synchronization");
+      }
       p->ws_pending = false;
     }
     if (p->d_ws) (void)hipFree(p->d_ws);
-    p->d_ws = nullptr;
-    p->ws_bytes = 0;
-    e = hipMalloc((void**)&p->d_ws, bytes);
-    if (e != hipSuccess) {
-      p->d_ws = nullptr;
-      (void)hipGetLastError();
-      if (e == hipErrorOutOfMemory) return XENG_ENOMEM;
-      return hip_fail(p, e, "hipMalloc (workspace)");
-    }
+    p->d_ws = grown;
     p->ws_bytes = bytes;
+    p->ws_refused = SIZE_MAX;
   } else if (p->ws_pending && p->ws_used) {
     e = hipStreamWaitEvent(s, p->ws_used, 0);
     if (e != hipSuccess) return hip_fail(p, e, "hipStreamWaitEvent");

@@ -1,0 +1,264 @@
+// The C ABI's host side on a model of the HIP runtime: no GPU, no device code.
+//
+// Streams, events and host waits carry vector clocks; every launch that works in
+// plan-owned memory has to come after all earlier ones in it, and memory is
+// freed only when its last use is known to have finished.  hipStreamPerThread is
+// another stream in every (model) thread, and a destroyed stream's handle is
+// given out again while its work still runs.  Run with a scenario's name.
+#include "xeng_api.cpp"
+
+#include <cstdio>
+#include <cstdlib>
+#include <functional>
+#include <map>
+#include <string>
+
+namespace model {
+using Clock = std::map<int, long>;  // stream -> operations known to be done
+void merge(Clock& a, const Clock& b) {
+  for (auto& x : b) a[x.first] = std::max(a[x.first], x.second);
+}
+struct Stream { int id; Clock seen; };
+struct Alloc { size_t bytes; int device; Clock uses; };
+int device = 0, thread = 0, next_id = 1;
+std::map<std::string, Stream> streams;        // by device, handle, thread, generation
+std::map<hipStream_t, int> generation, owner; // owner: device of an explicit stream
+std::map<hipStream_t, bool> capturing;
+bool null_in_capture = false;
+hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+Clock host;
+std::map<uintptr_t, Alloc> memory;
+size_t limit = 1ull << 40;
+int mallocs = 0, events = 0, waits = 0, work = 0, tiles = 0;
+size_t largest = 0;
+uintptr_t next_address = 1ull << 32;
+
+[[noreturn]] void fail(const char* what) {
+  std::printf("FAILED: %s\n", what);
+  std::exit(1);
+}
+int device_of(hipStream_t s) {
+  return s && s != hipStreamPerThread && owner.count(s) ? owner[s] : device;
+}
+Stream& stream(hipStream_t s) {
+  char key[96];
+  std::snprintf(key, sizeof key, "%d %p %d %d", device_of(s), (void*)s,
+                s == hipStreamPerThread ? thread : 0, generation[s]);
+  Stream& r = streams[key];
+  if (!r.seen.size()) r.id = next_id++;
+  return r;
+}
+Clock& step(hipStream_t s) {  // one operation queued on s; what is done before it and by it
+  Stream& r = stream(s);
+  merge(r.seen, host);
+  ++r.seen[r.id];
+  return r.seen;
+}
+void use(const void* p, hipStream_t s) {
+  auto it = memory.upper_bound((uintptr_t)p);
+  if (it == memory.begin()) fail("work in memory that was never allocated");
+  Alloc& a = (--it)->second;
+  if ((uintptr_t)p >= it->first + a.bytes) fail("work in memory that is not the plan's");
+  if (a.device != device_of(s)) fail("memory of one device used on another");
+  if (capturing[s]) fail("plan-owned memory used under capture");
+  const Clock c = step(s);
+  for (auto& u : a.uses) {
+    auto k = c.find(u.first);
+    if (k == c.end() || k->second < u.second) fail("two calls in the workspace at once");
+  }
+  a.uses[stream(s).id] = c.at(stream(s).id);
+  ++work;
+}
+bool refused_now() { return mode != hipStreamCaptureModeRelaxed && [] {
+    for (auto& c : capturing) if (c.second) return true;
+    return false; }(); }
+struct Event { Clock at; };
+}  // namespace model
+using namespace model;
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = device_of(s); return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) {
+  if (refused_now()) return hipErrorStreamCaptureUnsupported;
+  ++mallocs;
+  if (n > limit) return hipErrorOutOfMemory;
+  largest = std::max(largest, n);
+  *p = (void*)next_address;
+  memory[next_address] = Alloc{n, device, {}};
+  next_address += (n + 4095) / 4096 * 4096;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  auto it = memory.find((uintptr_t)p);
+  if (it == memory.end()) fail("freed twice or never allocated");
+  for (auto& u : it->second.uses)
+    if (host[u.first] < u.second) fail("memory freed while work in it may run");
+  memory.erase(it);
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t) new Event; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { delete (Event*)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  if (!s && null_in_capture) return hipErrorStreamCaptureImplicit;
+  ++events;
+  ((Event*)e)->at = step(s);
+  return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { ++waits; merge(host, ((Event*)e)->at); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { ++waits; merge(host, stream(s).seen); return hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+  ++waits;
+  for (auto& s : streams) merge(host, s.second.seen);
+  return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  merge(stream(s).seen, ((Event*)e)->at);
+  step(s);
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  if (!s && null_in_capture) return hipErrorStreamCaptureImplicit;
+  *st = capturing[s] ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) { std::swap(*m, mode); return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorName(hipError_t) { return ""; }
+const char* hipGetErrorString(hipError_t) { return ""; }
+// not reached by the scenarios
+#define UNUSED(decl) hipError_t decl { fail(__func__); }
+UNUSED(hipGraphDestroy(hipGraph_t)) UNUSED(hipGraphExecDestroy(hipGraphExec_t))
+UNUSED(hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t))
+UNUSED(hipGraphLaunch(hipGraphExec_t, hipStream_t)) UNUSED(hipHostFree(void*))
+UNUSED(hipHostMalloc(void**, size_t, unsigned)) UNUSED(hipMemcpy(void*, const void*, size_t, hipMemcpyKind))
+UNUSED(hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t))
+UNUSED(hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode))
+UNUSED(hipStreamCreateWithFlags(hipStream_t*, unsigned)) UNUSED(hipStreamDestroy(hipStream_t))
+UNUSED(hipStreamEndCapture(hipStream_t, hipGraph_t*))
+}
+
+namespace xeng {
+hipError_t launch_chan(const ChanArgs& a, bool, hipStream_t s) {
+  if (a.partial) use((char*)a.partial + 8LL * a.nslices * a.F * a.N * (a.N + 1) / 2 - 1, s);
+  return hipSuccess;
+}
+hipError_t launch_small(const ChanArgs& a, bool f, hipStream_t s) { return launch_chan(a, f, s); }
+int small_columns(int N) { return N <= 16 ? 16 : N <= 32 ? 32 : N <= 64 ? 64 : 128; }
+hipError_t launch_chan_reduce(const int32_t* p, int32_t*, long long, int, bool, hipStream_t s) { use(p, s); return hipSuccess; }
+hipError_t launch_pack(const PackArgs& a, bool, hipStream_t s) { use(a.packed, s); return hipSuccess; }
+hipError_t launch_packed(const PackedArgs& a, hipStream_t s) { use(a.packed, s); return hipSuccess; }
+hipError_t launch_tiles(const TileArgs&, int, bool, hipStream_t) { ++tiles; return hipSuccess; }
+hipError_t launch_zero(int32_t*, long long, hipStream_t) { return hipSuccess; }
+hipError_t launch_zero_tiles(int32_t*, int, int, int, int, int, hipStream_t) { return hipSuccess; }
+#undef UNUSED
+#define UNUSED(decl) hipError_t decl { fail(__func__); }
+UNUSED(launch_batch(const BatchInst*, int, const BatchItem*, int, int*, int, int, bool, hipStream_t))
+UNUSED(launch_beams(BeamArgs, int, bool, hipStream_t)) UNUSED(launch_flag_counts(const FlagArgs&, int, hipStream_t))
+UNUSED(launch_flag_scan(const FlagArgs&, int, int, hipStream_t)) UNUSED(launch_gated(const GatedArgs&, int, bool, hipStream_t))
+UNUSED(launch_noalloc_prep(const NoallocArgs&, hipStream_t))
+UNUSED(launch_normalize(const int32_t*, const int32_t*, long long, double, float*, hipStream_t))
+UNUSED(launch_shift_copy(const uint8_t*, uint8_t*, int, int, int, const int*, hipStream_t))
+UNUSED(launch_wide(const TileArgs&, int, hipStream_t)) UNUSED(noalloc_workspace(unsigned char**, int*))
+}  // namespace xeng
+
+namespace {
+struct Shape { int N, F, T; };
+// sliced small arrays, the sliced channel kernel, the packed path
+const Shape kShapes[] = {{40, 3, 8192}, {200, 2, 8192}, {704, 2, 11008}};
+hipStream_t handle(int k) { return (hipStream_t)(uintptr_t)(0x1000 * k); }
+uint8_t* const frame = (uint8_t*)0x10;
+int32_t* const vis = (int32_t*)0x20;
+struct Fixture {
+  xeng_plan_t p = nullptr;
+  Shape s;
+  explicit Fixture(Shape shape) : s(shape) {
+    if (xeng_plan(&p, s.N, s.F, s.T, 0) != XENG_OK) fail("plan");
+  }
+  // T samples on stream st: whether the call worked in plan-owned memory
+  bool call(hipStream_t st, int T = 0) {
+    const int w = work, t = tiles;
+    if (xeng_correlate(p, frame, s.N, s.F, T ? T : s.T, vis, st) != XENG_OK) fail("call refused");
+    if (work == w && tiles == t) fail("nothing launched");
+    return work > w;
+  }
+};
+void check(bool ok, const char* what) {
+  if (!ok) fail(what);
+}
+
+void streams_in_turn(Shape s) {
+  Fixture f(s);
+  for (int k = 0; k < 3; ++k) check(f.call(nullptr), "workspace path expected");
+  check(events == 0, "no events on the null stream");
+  for (int k : {1, 2, 1, 0, 2, 2, 0, 1}) check(f.call(handle(k)), "workspace path expected");
+  check(waits == 0 && mallocs == 1, "no host wait, one allocation");
+}
+void per_thread(Shape s) {
+  Fixture f(s);
+  for (int k = 0; k < 8; ++k) {
+    thread = k % 2;
+    check(f.call(hipStreamPerThread), "workspace path expected");
+  }
+  check(waits == 0, "no host wait");
+}
+void reused_handles(Shape s) {
+  Fixture f(s);
+  for (int k = 0; k < 4; ++k) {
+    check(f.call(handle(1)), "workspace path expected");
+    ++generation[handle(1)];
+  }
+}
+void growth(Shape s) {
+  for (hipStream_t st : {(hipStream_t) nullptr, handle(1)}) {
+    Fixture f(s);
+    f.call(st, s.T / 2);
+    check(f.call(handle(2), s.T / 2), "workspace path expected");
+    check(f.call(st), "workspace path expected");
+    check(f.call(handle(3), s.T / 2), "workspace path expected");
+  }
+}
+void refused(Shape s) {
+  Fixture f(s);
+  check(f.call(nullptr, s.T / 2), "workspace path expected");
+  limit = 1;
+  const int m = mallocs;
+  for (int k = 0; k < 40; ++k) {
+    check(!f.call(nullptr), "no memory, no workspace");
+    check(f.call(nullptr, s.T / 2), "the plan keeps the workspace it has");
+  }
+  check(mallocs == m + 1, "a refusal is remembered");
+  limit = 1ull << 40;
+  bool again = false;
+  for (int k = 0; k < 200 && !again; ++k) again = f.call(nullptr);
+  check(again, "asked for again");
+}
+void captured(Shape s) {
+  Fixture f(s);
+  check(f.call(nullptr), "workspace path expected");
+  capturing[handle(1)] = true;
+  check(!f.call(handle(1)), "captured calls take no workspace");
+  check(f.call(handle(2)), "beside a capture");
+  Fixture g(s);
+  check(g.call(handle(2)), "first call beside a capture");
+  // a capture that includes the null stream: its order cannot be recorded now
+  Fixture h(s);
+  check(h.call(nullptr), "workspace path expected");
+  null_in_capture = true;
+  check(!h.call(handle(2)), "no order after the null stream");
+  null_in_capture = false;
+  check(h.call(handle(2)), "workspace path expected");
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, std::function<void(Shape)>> all = {
+      {"streams_in_turn", streams_in_turn}, {"per_thread", per_thread},
+      {"reused_handles", reused_handles},   {"growth", growth},
+      {"refused", refused},                 {"captured", captured}};
+  if (argc != 3 || !all.count(argv[1])) return 2;
+  all.at(argv[1])(kShapes[std::atoi(argv[2])]);
+  std::printf("ok\n");
+  return 0;
+}
