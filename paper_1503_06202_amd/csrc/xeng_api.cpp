@@ -94,6 +94,7 @@ struct xeng_plan_s {
   // packed operands): plan-owned, grown on demand; see workspace()
   uint8_t* d_ws = nullptr;
   size_t ws_bytes = 0;
+  int ws_device = 0;
   // the size last refused for want of memory, asked for again after kRefusedCalls calls
   size_t ws_refused = SIZE_MAX;
   int ws_skipped = 0;
@@ -438,10 +439,19 @@ static int workspace_record(xeng_plan_t p, hipStream_t s) {
 // stream records the event for those before it.  An equal handle says nothing
 // on other streams: hipStreamPerThread is another one in every thread, and the
 // handles of destroyed streams are given out again.
-// XENG_ENOMEM: the call has to do without (no memory, or its order after the
-// null stream cannot be had while another stream's capture includes that one).
+// XENG_ENOMEM: the call has to do without (no memory, a stream of another device
+// than the memory's, or its order after the null stream cannot be had while
+// another stream's capture includes that one).
 static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
-  hipError_t e = hipSuccess;
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return hip_fail(p, e, "hipGetDevice");
+  if (s != nullptr) {
+    hipDevice_t own = device;
+    if (hipStreamGetDevice(s, &own) != hipSuccess) (void)hipGetLastError();
+    if (own != device) return XENG_ENOMEM;
+  }
+  if (p->d_ws && device != p->ws_device) return XENG_ENOMEM;
   if (p->ws_pending && !p->ws_used && s != nullptr) {
     if (stream_captures(nullptr)) return XENG_ENOMEM;
     const int rc = workspace_record(p, nullptr);
@@ -470,6 +480,7 @@ static int workspace(xeng_plan_t p, size_t bytes, hipStream_t s) {
     }
     if (p->d_ws) (void)hipFree(p->d_ws);
     p->d_ws = grown;
+    p->ws_device = device;
     p->ws_bytes = bytes;
     p->ws_refused = SIZE_MAX;
   } else if (p->ws_pending && p->ws_used) {

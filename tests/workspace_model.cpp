@@ -250,13 +250,25 @@ void captured(Shape s) {
   null_in_capture = false;
   check(h.call(handle(2)), "workspace path expected");
 }
+void two_devices(Shape s) {
+  Fixture f(s);
+  check(f.call(nullptr), "workspace path expected");
+  device = 1;
+  check(!f.call(nullptr), "not on another device");
+  owner[handle(1)] = 0, owner[handle(2)] = 1;
+  check(!f.call(handle(2)), "not on another device's stream");
+  check(!f.call(handle(1)), "nor while another device is current");
+  device = 0;
+  check(f.call(handle(1)) && f.call(nullptr), "workspace path expected");
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, std::function<void(Shape)>> all = {
       {"streams_in_turn", streams_in_turn}, {"per_thread", per_thread},
       {"reused_handles", reused_handles},   {"growth", growth},
-      {"refused", refused},                 {"captured", captured}};
+      {"refused", refused},                 {"captured", captured},
+      {"two_devices", two_devices}};
   if (argc != 3 || !all.count(argv[1])) return 2;
   all.at(argv[1])(kShapes[std::atoi(argv[2])]);
   std::printf("ok\n");
