@@ -790,14 +790,15 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   // 256, F = 64, T = 32768)
   bool chan = !kshift && N <= kChanMax &&
               (p->kernel == 5 ? p->form == XENG_FORM_I8 : p->kernel == 0 && N > kTile && fast);
+  int part_slices = 1;  // slices whose partial triangles this call's workspace holds
   if (small || chan) {
-    // the slices' partial triangles, for the longest launch; a call that
-    // cannot have them (no memory, or under capture) takes the tile kernels
-    const int ns = channel_slices(p, small, N, F, std::min(T, XENG_I8_SEG_MAX)).n;
-    if (ns > 1) {
+    // the slices' partial triangles, as many as the longest launch takes; a call
+    // that cannot have them (no memory, or under capture) takes the tile kernels
+    part_slices = channel_slices(p, small, N, F, std::min(T, XENG_I8_SEG_MAX)).n;
+    if (part_slices > 1) {
       rc = stream_captures(s)
                ? XENG_ENOMEM
-               : workspace(p, (size_t)ns * F * N * (N + 1) * sizeof(int32_t), s);
+               : workspace(p, (size_t)part_slices * F * N * (N + 1) * sizeof(int32_t), s);
       if (rc == XENG_ENOMEM) small = chan = false;
       else if (rc != XENG_OK) return rc;
     }
@@ -815,12 +816,12 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   for (int t0 = 0; t0 < T; t0 += seg) {
     const int t1 = std::min(T, t0 + seg), len = t1 - t0;
     if (chan || small) {
-      // a shorter last segment slices no finer than the first: its partial
-      // triangles fit
+      // a shorter last segment may want more slices than the first: not more than
+      // this call has a workspace for
       const Slices sc = channel_slices(p, small, N, F, len);
       const bool add = p->accumulate || t0 > 0;
       const long long part = (long long)F * N * (N + 1);  // ints of one slice's triangles
-      const int ns = std::min(sc.n, std::max(1, (int)(p->ws_bytes / (part * sizeof(int32_t)))));
+      const int ns = std::min(sc.n, part_slices);
       const int sl = ns == sc.n ? sc.len : ((len + ns - 1) / ns + kChunk - 1) / kChunk * kChunk;
       xeng::ChanArgs c;
       c.samples = samples;

@@ -29,7 +29,7 @@ hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 Clock host;
 std::map<uintptr_t, Alloc> memory;
 size_t limit = 1ull << 40;
-int mallocs = 0, events = 0, waits = 0, work = 0, tiles = 0;
+int mallocs = 0, events = 0, waits = 0, work = 0, tiles = 0, direct = 0;
 size_t largest = 0;
 uintptr_t next_address = 1ull << 32;
 
@@ -141,6 +141,7 @@ UNUSED(hipStreamEndCapture(hipStream_t, hipGraph_t*))
 
 namespace xeng {
 hipError_t launch_chan(const ChanArgs& a, bool, hipStream_t s) {
+  if (!a.partial) ++direct;  // writes vis itself
   if (a.partial) use((char*)a.partial + 8LL * a.nslices * a.F * a.N * (a.N + 1) / 2 - 1, s);
   return hipSuccess;
 }
@@ -178,9 +179,9 @@ struct Fixture {
   }
   // T samples on stream st: whether the call worked in plan-owned memory
   bool call(hipStream_t st, int T = 0) {
-    const int w = work, t = tiles;
+    const int w = work, t = tiles, d = direct;
     if (xeng_correlate(p, frame, s.N, s.F, T ? T : s.T, vis, st) != XENG_OK) fail("call refused");
-    if (work == w && tiles == t) fail("nothing launched");
+    if (work == w && tiles == t && direct == d) fail("nothing launched");
     return work > w;
   }
 };
@@ -261,6 +262,20 @@ void two_devices(Shape s) {
   device = 0;
   check(f.call(handle(1)) && f.call(nullptr), "workspace path expected");
 }
+void last_segment(Shape) {
+  // frames of several launches whose last one would take more slices than the
+  // first, which takes one and no workspace; the plan has one from another call
+  for (Shape s : {Shape{32, 438, 524288 + 515342}, Shape{65, 497, 524288 + 490511}}) {
+    Fixture f(s);
+    xeng_plan_set_tuning(f.p, 64, 0);
+    check(f.call(handle(1), 8192), "workspace path expected");
+    xeng_plan_set_tuning(f.p, 0, 0);
+    f.call(handle(2));
+    capturing[handle(2)] = true;
+    f.call(handle(2));
+    capturing[handle(2)] = false;
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -268,7 +283,7 @@ int main(int argc, char** argv) {
       {"streams_in_turn", streams_in_turn}, {"per_thread", per_thread},
       {"reused_handles", reused_handles},   {"growth", growth},
       {"refused", refused},                 {"captured", captured},
-      {"two_devices", two_devices}};
+      {"two_devices", two_devices},         {"last_segment", last_segment}};
   if (argc != 3 || !all.count(argv[1])) return 2;
   all.at(argv[1])(kShapes[std::atoi(argv[2])]);
   std::printf("ok\n");
