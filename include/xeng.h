@@ -114,7 +114,9 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * The small-array and channel kernels (see xeng_plan_set_tuning) with S > 1
  * time slices keep the slices' partial outputs, S F N(N+1) int32, in plan-owned
  * device memory allocated on first use (grown, after the plan's last call, when
- * S grows).
+ * S grows).  A named split_t whose partial outputs, here or on the packed path,
+ * would pass 1 GiB takes the tile kernels, unless the plan names the channel
+ * kernel.
  * Frames of more than 640 inputs and enough work take the packed path (unless
  * the plan names a kernel): the samples are repacked into FP6 operands (the
  * 4-bit codes are FP6 numbers as they stand) and correlated on FP6 matrix

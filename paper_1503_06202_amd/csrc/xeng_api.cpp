@@ -32,6 +32,11 @@ constexpr int kSplitMax = 128;
 // takes more on its own gets what it needs); larger frames run in groups of
 // channels.
 constexpr size_t kPackedMax = 4ull << 30;
+// Partial outputs of a slice count that the plan names, at most; more take the
+// tile kernels, whose slices add into vis (16 slices of 2048 inputs and 16
+// channels would store 5.4 GB, of 128 inputs and 1024 channels 1.1 GB).  The
+// automatic counts stay below it.
+constexpr size_t kPartMax = 1ull << 30;
 // Calls that do without a workspace after its memory was refused, before one
 // asks again: a refusal costs more than many a frame.
 constexpr int kRefusedCalls = 64;
@@ -506,6 +511,10 @@ static size_t packed_channel_bytes(int N, int len) {
   return steps * blocks * xeng::BLOCK_BYTES + nsum * blocks * kTile * sizeof(int2);
 }
 
+// The slice count that a plan names for its frames (batch plans name theirs per
+// instance, and those keep the tiles), or 0.
+static int named_slices(xeng_plan_t p) { return p->kind == PLAN_SINGLE ? p->split_t : 0; }
+
 // The packed path's schedule for W tiles of `plen` samples on `cus` compute
 // units (one workgroup each): uniform slices, or R full rounds of whole tiles
 // and the rest in slices that fill one more round.
@@ -620,7 +629,7 @@ static PackedNeed packed_need(xeng_plan_t p, int N, int F, int T) {
     const int plen = (len + xeng::PK_GRAIN - 1) / xeng::PK_GRAIN * xeng::PK_GRAIN;
     const PackedSchedule c =
         packed_schedule((long long)tpc * nch, plen, packed_sumb(blocks, nch, plen, p->cu_count),
-                        p->cu_count, p->split_t);
+                        p->cu_count, named_slices(p));
     const long long items = c.nslices > 1 ? c.head * c.nslices
                                           : ((long long)tpc * nch - c.head) * c.tail_slices;
     part = std::max(part, (size_t)items * xeng::PK_PART * sizeof(int2));
@@ -668,7 +677,7 @@ static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8
       if (e != hipSuccess) return hip_fail(p, e, "pack launch");
 
       const PackedSchedule c =
-          packed_schedule((long long)tpc * nch, plen, k.sumb, p->cu_count, p->split_t);
+          packed_schedule((long long)tpc * nch, plen, k.sumb, p->cu_count, named_slices(p));
       xeng::PackedArgs a;
       a.packed = k.packed;
       a.sums = k.sums;
@@ -698,6 +707,7 @@ static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8
 static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
                             int32_t* vis, hipStream_t s) {
   const PackedNeed need = packed_need(p, N, F, T);
+  if (named_slices(p) > 0 && need.part > kPartMax) return XENG_ENOMEM;
   int rc = workspace(p, need.operands + need.part, s);
   if (rc != XENG_OK) return rc;
   rc = launch_packed_path(p, need, samples, N, F, T, vis, s);
@@ -796,9 +806,10 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
     // that cannot have them (no memory, or under capture) takes the tile kernels
     part_slices = channel_slices(p, small, N, F, std::min(T, XENG_I8_SEG_MAX)).n;
     if (part_slices > 1) {
-      rc = stream_captures(s)
-               ? XENG_ENOMEM
-               : workspace(p, (size_t)part_slices * F * N * (N + 1) * sizeof(int32_t), s);
+      const size_t bytes = (size_t)part_slices * F * N * (N + 1) * sizeof(int32_t);
+      // (a plan that names the channel kernel has it)
+      const bool most = p->split_t > 0 && p->kernel == 0 && bytes > kPartMax;
+      rc = most || stream_captures(s) ? XENG_ENOMEM : workspace(p, bytes, s);
       if (rc == XENG_ENOMEM) small = chan = false;
       else if (rc != XENG_OK) return rc;
     }

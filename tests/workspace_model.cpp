@@ -276,6 +276,29 @@ void last_segment(Shape) {
     capturing[handle(2)] = false;
   }
 }
+void bounded_slices(Shape) {
+  // a slice count that the plan names does not take memory without bound
+  for (Shape s : {Shape{2048, 16, 32768}, Shape{128, 1024, 32768}}) {
+    Fixture f(s);
+    xeng_plan_set_tuning(f.p, 2, 0);
+    check(f.call(nullptr), "workspace path expected");
+    const size_t two = largest;
+    xeng_plan_set_tuning(f.p, 64, 0);
+    check(!f.call(nullptr), "tile kernels expected");
+    check(largest == two, "no more memory");
+  }
+  // the channel kernel, named, and automatic counts as they were
+  Fixture c({200, 64, 32768});
+  xeng_plan_set_tuning(c.p, 4, 5);
+  check(c.call(nullptr), "channel kernel expected");
+  for (int N : {641, 769, 1090, 2048, 4096, 8192})
+    for (int F : {1, 3, 16}) {
+      Fixture f({N, F, 16384});
+      largest = 0;
+      check(f.call(nullptr), "packed path expected");
+      check(largest <= (4ull << 30) + (1ull << 30), "operands and partial blocks");
+    }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -283,7 +306,8 @@ int main(int argc, char** argv) {
       {"streams_in_turn", streams_in_turn}, {"per_thread", per_thread},
       {"reused_handles", reused_handles},   {"growth", growth},
       {"refused", refused},                 {"captured", captured},
-      {"two_devices", two_devices},         {"last_segment", last_segment}};
+      {"two_devices", two_devices},         {"last_segment", last_segment},
+      {"bounded_slices", bounded_slices}};
   if (argc != 3 || !all.count(argv[1])) return 2;
   all.at(argv[1])(kShapes[std::atoi(argv[2])]);
   std::printf("ok\n");
