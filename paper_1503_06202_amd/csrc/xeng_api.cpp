@@ -55,6 +55,7 @@ struct xeng_plan_s {
   int split_t = 0;  // 0 = automatic
   int kernel = 0;   // 0 = automatic (packed path included), 1 = 128 x 128 tiles, 2 = 128 x 256 tiles,
                     // 3 / 4 = 128 x 128 tiles with split / common diagonal roles
+  bool once = false;  // see xeng_plan_once
   int cu_count = 0;
   std::string err;
 
@@ -703,11 +704,28 @@ static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8
   return XENG_OK;
 }
 
+// A plan that serves one call (the Python face's one-shot correlation; not part
+// of the C ABI in include/xeng.h): it takes no workspace whose allocation and
+// release the one call does not gain back.  Memory from 2 MiB on costs about 35
+// us, gigabytes 0.3 ms, less than 2 MiB nothing (one-shot calls, microseconds,
+// tiles / workspace): N = 64, F = 4, T = 16384 37 / 63, F = 64, T = 65536
+// 165 / 108; N = 128, F = 16, T = 16384 69 / 77; N = 200 (FP8), F = 4, T =
+// 16384 53 / 84, F = 16, T = 65536 213 / 168; packed, N = 2048: 3293 / 2729 on
+// 1.1e12 complex MACs, 202 / 428 on 1.7e10.
+void xeng_plan_once(xeng_plan_t p) { p->once = true; }
+
+static bool once_pays(xeng_plan_t p, size_t bytes, int N, int F, int T, bool packed) {
+  if (!p->once || bytes < (2u << 20)) return true;
+  if (packed) return 0.5 * N * (N + 1.0) * F * T >= 5e11;
+  return tiles_per_channel(N) * F * T >= (1 << 21);
+}
+
 // Correlate by the packed path (XENG_ENOMEM: nothing was queued).
 static int correlate_packed(xeng_plan_t p, const uint8_t* samples, int N, int F, int T,
                             int32_t* vis, hipStream_t s) {
   const PackedNeed need = packed_need(p, N, F, T);
   if (named_slices(p) > 0 && need.part > kPartMax) return XENG_ENOMEM;
+  if (!once_pays(p, need.operands + need.part, N, F, T, true)) return XENG_ENOMEM;
   int rc = workspace(p, need.operands + need.part, s);
   if (rc != XENG_OK) return rc;
   rc = launch_packed_path(p, need, samples, N, F, T, vis, s);
@@ -809,7 +827,9 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       const size_t bytes = (size_t)part_slices * F * N * (N + 1) * sizeof(int32_t);
       // (a plan that names the channel kernel has it)
       const bool most = p->split_t > 0 && p->kernel == 0 && bytes > kPartMax;
-      rc = most || stream_captures(s) ? XENG_ENOMEM : workspace(p, bytes, s);
+      rc = most || stream_captures(s) || !once_pays(p, bytes, N, F, T, false)
+               ? XENG_ENOMEM
+               : workspace(p, bytes, s);
       if (rc == XENG_ENOMEM) small = chan = false;
       else if (rc != XENG_OK) return rc;
     }

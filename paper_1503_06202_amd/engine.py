@@ -286,13 +286,8 @@ def correlate(samples: torch.Tensor, form: str = "i8", vis: Optional[torch.Tenso
               stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """One-shot correlation of a frame (plans, runs and frees a plan)."""
     T, F, N = _check_samples(samples)
-    # Above 640 inputs a plan may keep repacked operands, whose allocation and
-    # release take about 0.3 ms: a plan used once gains that back only on
-    # frames of some 4e11 complex MACs (2729 us against 3293 us on 1.1e12;
-    # 428 us against 202 us on 1.7e10)
-    if kernel == 0 and N > 640 and F * T * num_baselines(N) < 5e11:
-        kernel = 1
     with Plan(N, F, T, form=form, accumulate=accumulate, split_t=split_t, kernel=kernel) as p:
+        _lib.lib().xeng_plan_once(p.handle)  # no workspace that one call does not gain back
         return p.correlate(samples, vis, stream)
 
 

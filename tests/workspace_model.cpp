@@ -299,6 +299,19 @@ void bounded_slices(Shape) {
       check(largest <= (4ull << 30) + (1ull << 30), "operands and partial blocks");
     }
 }
+void one_shot(Shape) {
+  // a plan that serves one call: no workspace that the call does not gain back
+  struct { Shape s; bool workspace; } const calls[] = {
+      {{16, 1, 4096}, true},     {{64, 4, 8192}, false},    {{64, 64, 65536}, true},
+      {{128, 16, 16384}, false}, {{200, 4, 16384}, false},  {{200, 16, 65536}, true},
+      {{1024, 4, 8192}, false},  {{2048, 16, 32768}, true}, {{1024, 1, 8192}, false}};
+  for (auto& c : calls) {
+    Fixture f(c.s), kept(c.s);
+    xeng_plan_once(f.p);
+    check(f.call(nullptr) == c.workspace, "one-shot rule");
+    check(kept.call(nullptr), "kept plans take the workspace");
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -307,7 +320,8 @@ int main(int argc, char** argv) {
       {"reused_handles", reused_handles},   {"growth", growth},
       {"refused", refused},                 {"captured", captured},
       {"two_devices", two_devices},         {"last_segment", last_segment},
-      {"bounded_slices", bounded_slices}};
+      {"bounded_slices", bounded_slices},
+      {"one_shot", one_shot}};
   if (argc != 3 || !all.count(argv[1])) return 2;
   all.at(argv[1])(kShapes[std::atoi(argv[2])]);
   std::printf("ok\n");
