@@ -76,8 +76,11 @@ def lib() -> ctypes.CDLL:
     L.xeng_plan_set_tuning.restype = ci
     L.xeng_destroy.argtypes = [vp]
     L.xeng_destroy.restype = ci
-    L.xeng_plan_once.argtypes = [vp]  # not in include/xeng.h (see xeng_api.cpp)
+    # not in include/xeng.h (see xeng_api.cpp)
+    L.xeng_plan_once.argtypes = [vp]
     L.xeng_plan_once.restype = None
+    L.xeng_takes_packed.argtypes = [ci, ci, ci, ci]
+    L.xeng_takes_packed.restype = ci
     L.xeng_plan_error.argtypes = [vp]
     L.xeng_plan_error.restype = ctypes.c_char_p
     L.xeng_plan_batch.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(XengInstance), ci,

@@ -574,41 +574,127 @@ static PackedSchedule packed_schedule(long long W, int plen, int sumb, int cus, 
   return c;
 }
 
-// When the packed path is chosen (tuning kernel 0).  Packing moves 2.5 bytes of
-// HBM traffic a sample (0.52 ms for a GiB of samples) and the FP6 correlation
-// runs at about 1.8 times the rate of the int8 tiles, so it pays from about
-// 700 inputs; measured on frames of 512..2048 inputs, 1..64 channels and
-// 512..32768 samples (microseconds, tile kernels / packed path):
-//   N = 2048, F = 16, T = 32768  3275 / 2372    N = 768, F = 16, T = 32768  522 / 524
-//   N = 1024, F = 16, T = 32768   862 / 718     N = 512, F = 16, T = 32768  258 / 281
-// It takes three launches and at least 32 us, which small frames do not: below
-// 230,000 tile-samples (128 x 128 tiles x samples) the tile kernels win
-//   N = 1024, F = 1, T = 8192 (295,000)  63 / 49    T = 2048 (74,000)    30 / 40
-//   N = 768,  F = 1, T = 32768 (688,000) 79 / 71    T = 8192 (172,000)   45 / 50
-// and short integrations are bound by the visibilities, not the products:
-//   N = 2048, F = 16, T = 512  102 / 128    T = 2048  274 / 240
-//   N = 1776, F = 14, T = 1984 (1470 tiles, FP8)  155 / 163   T = 3072  222 / 217
-//   N = 768,  F = 32, T = 1984 (672 tiles)         86 / 101   T = 2560  141 / 124
-//   N = 1024, F = 16, T = 1536 (576 tiles)         65 / 53
-// so below 2560 samples it is taken from 1024 inputs on where the last wave of
-// tiles (512 workgroups run at a time) leaves a tenth of the slots or more unused.
-// Delays that differ inside a block of 128 inputs (shift_copy) cost the tile
-// kernels a copy of the frame that fetches every line eight times (1.39 ms a
-// GiB), and the packed path only a longer packing pass (0.93 ms): there it
-// pays from 128 inputs on,
-//   N = 128, F = 16, T = 32768  131 / 110    N = 384, F = 64, T = 4096   259 / 130
-//   N = 512, F = 4,  T = 8192 (328,000)  80 / 64    N = 512, F = 1, T = 32768 (328,000)  76 / 81
-static bool packed_pays(int N, int F, int T, bool shift_copy) {
-  const long long tiles = tiles_per_channel(N) * F, work = tiles * T;
-  const bool odd_wave = N >= 1024 && (tiles + 511) / 512 * 512 * 10 >= tiles * 11;
-  if (T < (shift_copy || odd_wave ? 1536 : 2560)) return false;
-  return shift_copy ? N >= 128 && work >= 340000 : N > 640 && work >= 230000;
+// The tile kernels' schedule of W tiles over len samples: uniform slices (the
+// count named, or auto_slices'), or a head/tail split: R full rounds of whole
+// tiles (plain stores or adds), then the remaining tiles cut into slices that
+// fill one more round (atomic adds into a cleared region), if the cost model of
+// auto_slices prefers it.
+struct TileSchedule {
+  int nslices, slice_len;
+  long long head;
+  int tail_slices, tail_len;
+};
+
+static TileSchedule tile_schedule(long long W, int len, int cus, int occupancy, int split_t,
+                                  bool wide) {
+  auto round_chunk = [](int l) { return (l + kChunk - 1) / kChunk * kChunk; };
+  int n = split_t > 0 ? split_t : auto_slices(W, len, cus, occupancy);
+  n = std::min(n, (len + kChunk - 1) / kChunk);
+  const int sl = round_chunk((len + n - 1) / n);
+  TileSchedule c{(len + sl - 1) / sl, sl, W, 0, 0};
+  const long long slots = (long long)cus * occupancy;
+  if (split_t == 0 && !wide && W > slots && W % slots != 0 && slots % 8 == 0) {
+    const long long R = W / slots, rem = W - R * slots;
+    const int smax = std::max(1, std::min(16, len / 1024));
+    int St = (int)std::min<long long>(smax, std::max<long long>(1, (slots + rem / 2) / rem));
+    const int tl = round_chunk((len + St - 1) / St);
+    St = (len + tl - 1) / tl;
+    const double cost_tail = (double)R + slice_cost(rem, St, slots, occupancy);
+    if (St > 1 && cost_tail < slice_cost(W, c.nslices, slots, occupancy) - 1e-9)
+      c = TileSchedule{1, len, R * slots, St, tl};
+  }
+  return c;
 }
 
 static int packed_sumb(int blocks, int nchan, int plen, int cus) {
   const long long wgs = (long long)blocks * nchan *
                         ((plen + xeng::PK_SUMB_LONG - 1) / xeng::PK_SUMB_LONG);
   return wgs >= 4LL * cus ? xeng::PK_SUMB_LONG : xeng::PK_SUMB_SHORT;
+}
+
+// Estimated microseconds of one launch of either path (F channels, len samples;
+// add: into vis).  Fitted to 1300 frames of 640..4096 inputs, 1..48 channels and
+// 1024..40000 samples, both paths timed on each: 5.4% (tiles) and 5.7% (packed)
+// rms.  A round's last, partial wave counts as in round_cost, but 0.65 of a round
+// for lone workgroups and, after full rounds, three tenths in proportion to its
+// size; stores and atomic adds hide behind long items (half of them at 4000
+// samples).
+static double tiles_us(int N, int F, int len, bool add, int cus) {
+  const long long W = tiles_per_channel(N) * F, slots = (long long)cus * kOccupancy;
+  const TileSchedule c = tile_schedule(W, len, cus, kOccupancy, 0, false);
+  const double mb = 4e-6 * F * N * (N + 1.0);  // visibilities
+  auto rounds = [&](long long items) {
+    const long long full = items / slots, rem = items % slots;
+    double part = rem == 0 ? 0.0 : rem * kOccupancy <= slots ? 0.65 : 1.0;
+    if (full > 0) part = 0.3 * rem / slots + 0.7 * part;
+    return full + part;
+  };
+  auto shown = [](double samples) { return 4000.0 / (4000.0 + samples); };
+  double samples, stored = 0.0, added = 0.0;
+  if (c.tail_slices > 0) {
+    const double part = (double)(W - c.head) / W;
+    samples = (double)(c.head / slots) * len + rounds((W - c.head) * c.tail_slices) * c.tail_len;
+    stored = mb * (1.0 - part) * shown(len);
+    added = mb * part * c.tail_slices * shown(c.tail_len);
+  } else {
+    samples = rounds(W * c.nslices) * c.slice_len;
+    (c.nslices > 1 ? added : stored) = mb * c.nslices * shown(c.slice_len);
+  }
+  return 8.2 + 0.0210 * samples + (add ? 0.282 : 0.1185) * stored + 1.457 * added +
+         (c.nslices > 1 ? 2.4 : 0.0) + 0.0765 * mb;
+}
+
+static double packed_us(int N, int F, int len, bool add, int cus) {
+  const int blocks = (N + kTile - 1) / kTile;
+  const int plen = (len + xeng::PK_GRAIN - 1) / xeng::PK_GRAIN * xeng::PK_GRAIN;
+  const long long W = (long long)xeng::packed_tiles(blocks) * F;
+  const PackedSchedule c = packed_schedule(W, plen, packed_sumb(blocks, F, plen, cus), cus, 0);
+  auto rounds = [&](long long items) { return (double)((items + cus - 1) / cus); };
+  const double head = rounds(c.head * c.nslices);
+  const double tail = c.tail_slices > 0 ? rounds((W - c.head) * c.tail_slices) : 0.0;
+  const long long sliced = c.nslices > 1      ? W * c.nslices
+                           : c.tail_slices > 0 ? (W - c.head) * c.tail_slices
+                                               : 0;
+  const double mb = 4e-6 * F * N * (N + 1.0);
+  return 7.1 + (0.374 / xeng::PK_STEP) * (head * c.slice_len + tail * c.tail_len) +
+         16.6 * (head + tail) + 0.434e-6 * plen * F * blocks * kTile + 0.031 * mb +
+         (add ? 0.289 * mb : 0.0) + 0.038 * sliced;
+}
+
+// When the packed path is chosen (tuning kernel 0): where its estimate is the
+// lower one, by 3% for the estimates' errors.  Packing moves 2.5 bytes of HBM
+// traffic a sample (0.52 ms for a GiB of samples) and the FP6 correlation runs
+// at about 1.8 times the rate of the int8 tiles, so it pays from about 700 inputs
+// on; its three launches, and visibilities that bind short integrations alike,
+// leave the tiles ahead on small frames.  Microseconds, tile kernels / packed path:
+//   N = 2048, F = 16, T = 32768  3275 / 2372    N = 512, F = 16, T = 32768  258 / 281
+//   N = 1024, F = 16, T = 32768   862 / 718     N = 1024, F = 1, T = 8192    63 / 49
+//   N = 768,  F = 1, T = 32768     79 / 71      N = 768,  F = 1, T = 8192    45 / 50
+//   N = 1426, F = 2, T = 1577 39 / 60   N = 1152, F = 25, T = 1728 113 / 127
+//   N = 976, F = 41, T = 2944 229 / 288 N = 1281, F = 2, T = 2600   68 / 59
+// Of 800 other frames, drawn alike, 22 run more than 1% slower than on the tiles
+// for it, 1.12 times at most; lines in the size alone (2560 samples, or 1536 where
+// the tiles' last wave leaves a tenth of the slots unused) had 130 of 1300, up to
+// 1.55 times.  Below 230,000 tile-samples (128 x 128 tiles x samples) the
+// estimates are not close enough.
+// Delays that differ inside a block of 128 inputs (shift_copy) cost the tile
+// kernels a copy of the frame that fetches every line eight times (1.39 ms a
+// GiB), and the packed path only a longer packing pass (0.93 ms): there it
+// pays from 128 inputs on,
+//   N = 128, F = 16, T = 32768  131 / 110    N = 384, F = 64, T = 4096   259 / 130
+//   N = 512, F = 4,  T = 8192 (328,000)  80 / 64    N = 512, F = 1, T = 32768 (328,000)  76 / 81
+static bool packed_pays(int N, int F, int T, bool shift_copy, int form, bool add, int cus) {
+  const long long work = tiles_per_channel(N) * F * T;
+  if (shift_copy) return N >= 128 && T >= 1536 && work >= 340000;
+  if (N <= 640 || T < 1024 || work < 230000) return false;
+  auto total = [&](auto&& us, int seg) {
+    const int full = T / seg, rest = T % seg;
+    double t = full > 0 ? us(seg, add) + (full - 1) * us(seg, true) : 0.0;
+    return rest > 0 ? t + us(rest, add || full > 0) : t;
+  };
+  return total([&](int len, bool a) { return packed_us(N, F, len, a, cus); }, XENG_F8_FLUSH_MAX) <
+         0.97 * total([&](int len, bool a) { return tiles_us(N, F, len, a, cus); },
+                      segment_max(form));
 }
 
 // Workspace of a packed call: channels per group, operands and partial blocks
@@ -704,6 +790,12 @@ static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8
   return XENG_OK;
 }
 
+// Whether an automatic plan takes such a frame by the packed path (for the
+// benchmark's labels; not part of the C ABI in include/xeng.h).
+int xeng_takes_packed(int N, int F, int T, int form) {
+  return packed_pays(N, F, T, false, form, false, cu_count_hint());
+}
+
 // A plan that serves one call (the Python face's one-shot correlation; not part
 // of the C ABI in include/xeng.h): it takes no workspace whose allocation and
 // release the one call does not gain back.  Memory from 2 MiB on costs about 35
@@ -792,7 +884,8 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   int rc = ensure_cu_count(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->kernel == 0 && packed_pays(N, F, T, p->shift && p->shift_copy) && !stream_captures(s)) {
+  if (p->kernel == 0 && packed_pays(N, F, T, p->shift && p->shift_copy, p->form, p->accumulate, p->cu_count) &&
+      !stream_captures(s)) {
     rc = correlate_packed(p, samples, N, F, T, vis, s);
     if (rc != XENG_ENOMEM) return rc;
     // no room for the operands: the tile kernels need none
@@ -880,36 +973,8 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
       continue;
     }
     const long long W = tpc * F;  // tiles of the launch
-    int nslices = p->split_t > 0 ? p->split_t : auto_slices(W, len, p->cu_count, occupancy);
-    nslices = std::min(nslices, (len + kChunk - 1) / kChunk);
-    int slice_len = (len + nslices - 1) / nslices;
-    slice_len = (slice_len + kChunk - 1) / kChunk * kChunk;
-    nslices = (len + slice_len - 1) / slice_len;
     const bool add = p->accumulate || t0 > 0;
-
-    // Automatic choice between uniform slices and a head/tail split: R full
-    // rounds of whole tiles (plain stores or adds), then the remaining tiles
-    // cut into S_t slices that fill one more round (atomic adds into a
-    // cleared region).  Same cost model as auto_slices.
-    const long long slots = (long long)p->cu_count * occupancy;
-    long long head = W;
-    int tail_slices = 0, tail_len = 0;
-    if (p->split_t == 0 && !wide && W > slots && W % slots != 0 && slots % 8 == 0) {
-      const long long R = W / slots, rem = W - R * slots;
-      const int smax = std::max(1, std::min(16, len / 1024));
-      int St = (int)std::min<long long>(smax, std::max<long long>(1, (slots + rem / 2) / rem));
-      int tl = (len + St - 1) / St;
-      tl = (tl + kChunk - 1) / kChunk * kChunk;
-      St = (len + tl - 1) / tl;
-      const double cost_tail = (double)R + slice_cost(rem, St, slots, occupancy);
-      if (St > 1 && cost_tail < slice_cost(W, nslices, slots, occupancy) - 1e-9) {
-        head = R * slots;
-        tail_slices = St;
-        tail_len = tl;
-        nslices = 1;
-        slice_len = len;
-      }
-    }
+    const TileSchedule sch = tile_schedule(W, len, p->cu_count, occupancy, p->split_t, wide);
 
     xeng::TileArgs a;
     a.samples = samples;
@@ -920,13 +985,13 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
     a.t1 = t1;
     a.nt = nt;
     a.tiles_per_chan = (int)tpc;
-    a.nslices = nslices;
-    a.slice_len = slice_len;
+    a.nslices = sch.nslices;
+    a.slice_len = sch.slice_len;
     a.row_stride = (long long)F * N;
     a.t_frame = T;
-    a.head_tiles = (int)head;
-    a.tail_slices = tail_slices;
-    a.tail_len = tail_len;
+    a.head_tiles = (int)sch.head;
+    a.tail_slices = sch.tail_slices;
+    a.tail_len = sch.tail_len;
     a.tail_mode = xeng::WM_ATOMIC;
     // Diagonal tiles split the sub-tile above the diagonal between two waves
     // where they are a large share of the tiles (N <= 1024: at least 2 in 9);
@@ -935,7 +1000,7 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
     a.split_diag = p->kernel == 3 ? 1 : p->kernel == 4 ? 0 : (nt <= 8 ? 1 : 0);
     a.seg_delay = kshift ? p->d_seg_delay : nullptr;
     a.blk_delay = kshift ? p->d_blk_delay : nullptr;
-    if (nslices > 1) {
+    if (sch.nslices > 1) {
       a.write_mode = xeng::WM_ATOMIC;
       if (!add) {
         hipError_t e = xeng::launch_zero(vis, (long long)F * N * (N + 1), s);
@@ -944,8 +1009,9 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
     } else {
       a.write_mode = add ? xeng::WM_ADD : xeng::WM_STORE;
     }
-    if (tail_slices > 0 && !add) {
-      hipError_t e = xeng::launch_zero_tiles(vis, N, (int)tpc, nt, (int)head, (int)(W - head), s);
+    if (sch.tail_slices > 0 && !add) {
+      hipError_t e = xeng::launch_zero_tiles(vis, N, (int)tpc, nt, (int)sch.head,
+                                             (int)(W - sch.head), s);
       if (e != hipSuccess) return hip_fail(p, e, "tail zero launch");
     }
     hipError_t e = wide ? xeng::launch_wide(a, p->form, s) : xeng::launch_tiles(a, p->form, fast, s);
@@ -1313,10 +1379,11 @@ int xeng_beamform(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, in
 //   8 x (1024, 4, 32768)  4.7 M  1679 / 1631    6 x (2048, 2, 8192)   2.2 M  614 / 647
 //   2 x (1024, 4, 16384)  2.4 M   262 / 237     2 x (1024, 2, 16384)  1.2 M  183 / 142
 // A named slice count keeps the tiles.
-static bool batch_packs(const xeng_instance& d, long long batch_tiles, int slots) {
+static bool batch_packs(const xeng_instance& d, long long batch_tiles, int form, bool add,
+                        int cus) {
   const long long work = tiles_per_channel(d.N) * d.F * (long long)d.T;
-  return d.split_t == 0 && packed_pays(d.N, d.F, d.T, false) &&
-         work >= (batch_tiles > slots ? 4000000 : 1100000);
+  return d.split_t == 0 && packed_pays(d.N, d.F, d.T, false, form, add, cus) &&
+         work >= (batch_tiles > cus * kOccupancy ? 4000000 : 1100000);
 }
 
 int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, unsigned flags) {
@@ -1399,7 +1466,7 @@ int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, uns
       long long tiles = 0;
       for (int k = 0; k < count; ++k) tiles += descs[k].F * tiles_per_channel(descs[k].N);
       for (int k = 0; k < count; ++k) {
-        if (batch_packs(descs[k], tiles, cu_count_hint() * kOccupancy))
+        if (batch_packs(descs[k], tiles, p->form, p->accumulate, cu_count_hint()))
           p->large.push_back(k);
         else
           others.push_back(descs[k]);

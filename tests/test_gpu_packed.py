@@ -187,3 +187,13 @@ def test_captured_call_equals_eager():
             assert np.array_equal(vis.cpu().numpy(), want(src))
             assert np.array_equal(other.cpu().numpy(), want(y))
         del g
+
+
+@pytest.mark.parametrize("form", ["i8", "f8"])
+@pytest.mark.parametrize("N,T,F", [(1100, 32768 + 3 * 64 + 5, 1),  # two segments, an odd block count
+                                   (1090, 2049, 4), (2048, 2048, 4),  # short frames
+                                   (641, 7001, 6)])
+def test_packed_segments_and_short_frames(N, T, F, form):
+    s = rand_frame(N + T, T, F, N)
+    print(f"packed N={N} F={F} T={T} form={form}", flush=True)
+    assert np.array_equal(gpu(s, form), want(s))

@@ -24,7 +24,7 @@ def model(tmp_path_factory):
 
 @pytest.mark.parametrize("shape", [0, 1, 2], ids=["small", "channel", "packed"])
 @pytest.mark.parametrize("scenario", ["streams_in_turn", "per_thread", "reused_handles", "growth",
-                                      "refused", "captured", "two_devices", "last_segment", "bounded_slices", "one_shot"])
+                                      "refused", "captured", "two_devices", "last_segment", "bounded_slices", "one_shot", "paths"])
 def test_workspace(model, scenario, shape):
     res = subprocess.run([model, scenario, str(shape)], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0 and res.stdout == "ok\n", res.stdout + res.stderr
