@@ -875,6 +875,21 @@ static Slices channel_slices(xeng_plan_t p, bool small, int N, int F, int len) {
   return best;
 }
 
+// Estimated microseconds of the channel kernel, as tiles_us; fitted to 700 frames
+// of 129..256 inputs, 1..64 channels and 64..65536 samples (9% rms; tiles_us is
+// within 16% there).  Short integrations pay for its epilogue (FP8 form, tiles /
+// channel kernel: N = 240, F = 56, T = 1843, accumulated 42 / 71; N = 208, F = 8,
+// T = 273, accumulated 17 / 28; N = 240, F = 1, T = 205 14 / 19; but N = 256, F =
+// 64, T = 32768 297 / 222).
+static double channel_us(xeng_plan_t p, int N, int F, int len, bool add) {
+  const Slices c = channel_slices(p, false, N, F, len);
+  const long long items = (long long)F * c.n;
+  const double mb = 4e-6 * F * N * (N + 1.0);
+  const double t = 13.4 + 0.875 * ((items + p->cu_count - 1) / p->cu_count) * (c.len / kChunk) +
+                   0.293 * mb;
+  return c.n > 1 ? t + 2.3 + 0.484 * c.n * mb : add ? t + 7.5 + 0.283 * mb : t;
+}
+
 int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, int32_t* vis,
                    void* stream) {
   if (!p || !samples || !vis || N < 1 || F < 1 || T < 1) return XENG_EINVAL;
@@ -907,10 +922,13 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   // the small-array kernel: automatically up to one tile edge (both forms)
   bool small = p->kernel == 0 && !kshift && N <= kTile;
   // the channel kernel (N <= 256): on request (int8), or automatically above
-  // one tile edge (both forms: 222 us in int8 against 297 us on FP8 tiles, N =
-  // 256, F = 64, T = 32768)
+  // one tile edge; in the FP8 form where it is faster than that form's tiles
   bool chan = !kshift && N <= kChanMax &&
               (p->kernel == 5 ? p->form == XENG_FORM_I8 : p->kernel == 0 && N > kTile && fast);
+  if (chan && p->form == XENG_FORM_F8 && p->split_t == 0) {
+    const int len = std::min(T, XENG_F8_FLUSH_MAX);
+    chan = channel_us(p, N, F, len, p->accumulate) < tiles_us(N, F, len, p->accumulate, p->cu_count);
+  }
   int part_slices = 1;  // slices whose partial triangles this call's workspace holds
   if (small || chan) {
     // the slices' partial triangles, as many as the longest launch takes; a call

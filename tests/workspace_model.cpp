@@ -174,8 +174,8 @@ int32_t* const vis = (int32_t*)0x20;
 struct Fixture {
   xeng_plan_t p = nullptr;
   Shape s;
-  explicit Fixture(Shape shape) : s(shape) {
-    if (xeng_plan(&p, s.N, s.F, s.T, 0) != XENG_OK) fail("plan");
+  explicit Fixture(Shape shape, unsigned flags = 0) : s(shape) {
+    if (xeng_plan(&p, s.N, s.F, s.T, flags) != XENG_OK) fail("plan");
   }
   // T samples on stream st: whether the call worked in plan-owned memory
   bool call(hipStream_t st, int T = 0) {
@@ -311,6 +311,19 @@ void paths(Shape) {
     if (f.call(nullptr) != c.packed) std::printf("N %d F %d T %d: ", c.s.N, c.s.F, c.s.T);
     check((work > 0) == c.packed, "the slower path");
     work = 0;
+  }
+  // FP8 frames of 129..256 inputs: tiles, or the channel kernel
+  const unsigned f8 = XENG_FORM_F8, add = XENG_FORM_F8 | XENG_ACCUMULATE;
+  struct { Shape s; unsigned flags; bool tiles; } const mid[] = {
+      {{240, 56, 1843}, add, true}, {{208, 8, 273}, add, true},   {{240, 1, 205}, f8, true},
+      {{160, 49, 441}, add, true},  {{256, 64, 32768}, f8, false}, {{200, 16, 65536}, f8, false},
+      {{200, 8, 273}, XENG_FORM_I8, false}};
+  for (auto& c : mid) {
+    Fixture f(c.s, c.flags);
+    tiles = 0;
+    f.call(nullptr);
+    if ((tiles > 0) != c.tiles) std::printf("N %d F %d T %d: ", c.s.N, c.s.F, c.s.T);
+    check((tiles > 0) == c.tiles, "the slower path");
   }
 }
 void one_shot(Shape) {
