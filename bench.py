@@ -537,7 +537,7 @@ def main():
     import torch
 
     import synth
-    from paper_1503_06202_amd import Plan, vis_shape
+    from paper_1503_06202_amd import Plan, _lib, vis_shape
 
     if not torch.cuda.is_available():
         print("bench.py needs a GPU", file=sys.stderr)
@@ -579,7 +579,7 @@ def main():
     achieved = ops_per_launch / (ev_avg / 1e3) / 1e12
     # large frames of more than 640 inputs run on FP6 operands (both forms; the
     # 4-bit codes are FP6 numbers as they stand): priced against the FP6 peak
-    packed = w.N > 640 and w.T >= 2560
+    packed = bool(_lib.lib().xeng_takes_packed(w.N, w.F, w.T, {"i8": 0, "f8": 1}[args.form]))
     peak = PEAK_TOPS["f6" if packed else args.form]
     frame_s = w.T * SAMPLE_PERIOD_S
     channels_rt = w.F * frame_s / (ms_step / 1e3)
@@ -608,13 +608,15 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "int8" if args.form == "i8" else "fp8-e4m3",
+        # what the matrix cores multiply; results are exact int32 in every form
+        "dtype": "fp6-e2m3" if packed else "int8" if args.form == "i8" else "fp8-e4m3",
         "mfma_operands": "fp6-e2m3 (exact 4-bit codes)" if packed else args.form,
         "data": "synthetic",
         "config": {"workload": w.name, "N": w.N, "F": w.F, "T": w.T, "recipe": w.kind,
                    "seed": w.seed, "form": args.form, "baselines_per_channel": w.baselines,
                    "parallelism": "single GPU (channels independent)"},
-        "pct_mfma_peak": 100.0 * achieved / PEAK_TOPS[args.form],
+        "pct_mfma_peak": 100.0 * achieved / peak,
+        "pct_int8_mfma_peak": 100.0 * achieved / PEAK_TOPS["i8"],
         "realtime_channels": channels_rt,
         "mhz_per_gpu": channels_rt * CHANNEL_MHZ,
         "kernel_ms_avg": ev_avg,
@@ -699,9 +701,8 @@ def main():
         ceil = mfma_ceiling()
         if ceil:
             out["mfma_ceiling"] = ceil
-            key = "i8-codes" if args.form == "i8" else "f8-codes"
-            # (the probe has no FP6 loop to set a packed frame beside)
-            if not packed and key in ceil and ceil[key].get("tops"):
+            key = "f6-codes" if packed else "i8-codes" if args.form == "i8" else "f8-codes"
+            if key in ceil and ceil[key].get("tops"):
                 out["roofline"]["frac_of_measured_ceiling"] = achieved / ceil[key]["tops"]
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(frame, w)

@@ -65,10 +65,12 @@ enum {
 
 /* Flags of xeng_plan / xeng_plan_batch. */
 enum {
-    XENG_FORM_I8 = 0,        /* int8 MFMA, int32 accumulators (default) */
-    XENG_FORM_F8 = 1,        /* FP8 e4m3 MFMA, f32 accumulators flushed to int32; both forms
-                                are exact, and both take the packed path (FP6) where
-                                xeng_correlate chooses it */
+    XENG_FORM_I8 = 0,        /* tiles: int8 MFMA, int32 accumulators (default) */
+    XENG_FORM_F8 = 1,        /* tiles: FP8 e4m3 MFMA, f32 accumulators flushed to int32.
+                                Both forms are exact, and where xeng_correlate chooses
+                                them both take the small-array and channel kernels (int8)
+                                and the packed path (FP6 e2m3 operands, which hold every
+                                4-bit code, and f32 sums that stay below 2^24) */
     XENG_FORM_MASK = 0xff,
     XENG_ACCUMULATE = 1 << 8, /* add into vis instead of overwriting it */
     XENG_SHARED_VIS = 1 << 9  /* batch plans only, with XENG_ACCUMULATE: instances may share
@@ -307,7 +309,7 @@ int xeng_normalize(xeng_plan_t p, const int32_t *vis, const int32_t *counts, dou
  *
  * xeng_beamform: beams, device int32 [T][F][B][2] (re, im), from samples
  * [T][F][N] (device, layout above).  Asynchronous on `stream`.  Every sample
- * byte is read once per 64 beams (one launch covers up to 64 beams).
+ * byte is read once per 96 beams (one launch covers up to 96 beams).
  * Errors: XENG_EINVAL (NULL pointer, sizes < 1), XENG_EPLAN (not a beam plan,
  * no weights set, N or F other than planned, T > T_max), XENG_EHIP.
  */
@@ -353,7 +355,10 @@ int xeng_plan_batch(xeng_plan_t *out, const xeng_instance *descs, int count, uns
  * Correlate every instance of a batch plan (the definition of
  * xeng_correlate, Sec. IV-C "Full Correlation", per instance): samples[k] and
  * vis[k] are the device buffers of instance k (host arrays of count device pointers).  One
- * persistent kernel launch covers all instances.  An instance whose samples[k]
+ * persistent kernel launch covers all instances, but for the largest frames
+ * (named slice counts, XENG_SHARED_VIS and calls under capture aside), which
+ * follow it on the stream one by one by the packed path of xeng_correlate, with
+ * its plan-owned memory.  An instance whose samples[k]
  * is NULL is skipped by this call (its vis[k] is ignored and untouched), so a
  * plan over a pool of slots serves any subset of them.  Pointers are copied to
  * the device through plan-owned pinned staging on the given stream (a ring
@@ -369,7 +374,9 @@ int xeng_correlate_batch(xeng_plan_t p, const uint8_t *const *samples, int32_t *
 /*
  * As xeng_correlate_batch, replaying a HIP graph captured on the first call
  * for this exact array of pointers (re-captured when any pointer changes).
- * For fixed slot buffers, a call is one hipGraphLaunch.
+ * For fixed slot buffers, a call is one hipGraphLaunch, followed by plain
+ * launches where instances take the packed path (see xeng_correlate_batch).  Under
+ * capture the call is xeng_correlate_batch: its kernels are captured.
  */
 int xeng_correlate_batch_graph(xeng_plan_t p, const uint8_t *const *samples,
                                int32_t *const *vis, void *stream);

@@ -10,6 +10,7 @@
 //   i8-codes   int8 codes u = v + 8 (0..15), as the 128 x 128 int8 kernel
 //   i8-signed  int8 values v, for comparison
 //   f8-codes   FP8 e4m3 bytes u (u * 2^-9, scale 2^9), as the FP8 kernel
+//   f6-codes   FP6 e2m3 numbers u / 8 (the code's bits), as the packed kernel
 //
 // The matrix cores' power depends on the operand bits, so this, not the data
 // sheet's dense peak, is the throughput a correlation can reach on this chip.
@@ -31,7 +32,8 @@ constexpr int MAX_BLOCKS = 4096;
 
 __device__ long long g_clk[MAX_BLOCKS * 2];
 
-template <int F8>
+// FORM: 0 = int8, 1 = FP8, 2 = FP6
+template <int FORM>
 __global__ void __launch_bounds__(256, 2) ceiling_kernel(int iters, const v8i* __restrict__ data,
                                                          int* sink) {
   v8i a[NSET], b[NSET];
@@ -56,7 +58,9 @@ __global__ void __launch_bounds__(256, 2) ceiling_kernel(int iters, const v8i* _
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const v8i A = a[(i + j) % NSET], B = b[(3 * i + j) % NSET];
-        if (F8)
+        if (FORM == 2)
+          fc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, fc[i], 2, 2, 0, 0, 0, 0);
+        else if (FORM == 1)
           fc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, fc[i], 0, 0, 0, 136, 0, 136);
         else
           c[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_shufflevector(A, A, 0, 1, 2, 3),
@@ -99,9 +103,9 @@ int main() {
   hipEventCreate(&e1);
   std::vector<long long> clk(MAX_BLOCKS * 2);
   std::vector<unsigned> h((size_t)nv * 8);
-  const char* names[3] = {"i8-codes", "i8-signed", "f8-codes"};
+  const char* names[4] = {"i8-codes", "i8-signed", "f8-codes", "f6-codes"};
   std::printf("{\"grid\": %d, \"cus\": %d", grid, cus);
-  for (int kind = 0; kind < 3; ++kind) {
+  for (int kind = 0; kind < 4; ++kind) {
     for (int e = 0; e < nv * 8; ++e) {
       unsigned w = 0;
       for (int q = 0; q < 4; ++q) {
@@ -111,11 +115,26 @@ int main() {
       }
       h[e] = w;
     }
+    if (kind == 3) {  // a lane's 32 codes of six bits in its first six words (the MFMA reads no more)
+      for (int lane = 0; lane < nv; ++lane) {
+        unsigned* o = &h[(size_t)lane * 8];
+        for (int e = 0; e < 8; ++e) o[e] = 0;
+        for (int q = 0; q < 32; ++q) {
+          const unsigned long long u = (unsigned)(vals[(size_t)lane * 32 + q] + 8);
+          const unsigned long long w = u << (6 * q % 32);
+          o[6 * q / 32] |= (unsigned)w;
+          if (w >> 32) o[6 * q / 32 + 1] |= (unsigned)(w >> 32);
+        }
+      }
+    }
     hipMemcpy(d, h.data(), (size_t)nv * 32, hipMemcpyHostToDevice);
     double best_tops = 0, best_mhz = 0;
     for (int rep = 0; rep < 3; ++rep) {
       hipEventRecord(e0);
-      if (kind == 2)
+      if (kind == 3)
+        hipLaunchKernelGGL(ceiling_kernel<2>, dim3(grid), dim3(256), 0, 0, iters, (const v8i*)d,
+                           sink);
+      else if (kind == 2)
         hipLaunchKernelGGL(ceiling_kernel<1>, dim3(grid), dim3(256), 0, 0, iters, (const v8i*)d,
                            sink);
       else
@@ -131,7 +150,7 @@ int main() {
         cyc += (double)clk[2 * blk];
         rt += (double)clk[2 * blk + 1];
       }
-      const double macs = kind == 2 ? 32.0 * 32 * 64 : 32.0 * 32 * 32;
+      const double macs = kind >= 2 ? 32.0 * 32 * 64 : 32.0 * 32 * 32;
       const double ops = 2.0 * macs * 8 * iters * (grid * 4.0);
       const double tops = ops / ms / 1e9;
       if (rep > 0 && tops > best_tops) {

@@ -927,7 +927,9 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
               (p->kernel == 5 ? p->form == XENG_FORM_I8 : p->kernel == 0 && N > kTile && fast);
   if (chan && p->form == XENG_FORM_F8 && p->split_t == 0) {
     const int len = std::min(T, XENG_F8_FLUSH_MAX);
-    chan = channel_us(p, N, F, len, p->accumulate) < tiles_us(N, F, len, p->accumulate, p->cu_count);
+    // (the tiles have to be ahead by a tenth, for the estimates' errors)
+    chan = channel_us(p, N, F, len, p->accumulate) <
+           1.1 * tiles_us(N, F, len, p->accumulate, p->cu_count);
   }
   int part_slices = 1;  // slices whose partial triangles this call's workspace holds
   if (small || chan) {

@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(64 * NW) beam_kernel(BeamArgs a) {
     off[j] = (int)((ALIGNED ? tbase + 32 * j + r : min(tbase + 32 * j + r, a.T - 1)) * row_stride) +
              16 * h;
   // A step's weights are 8 x NB x 64 operands; thread tid stages operands
-  // e = tid + 256 k, k < 2 NB, with e = (q NB + c) 64 + lane.
+  // e = tid + 64 NW k, k < WT, with e = (q NB + c) 64 + lane.
   auto wsrc = [&](int s, int e) {
     const int l = e & 63, c = (e >> 6) % NB, q = (e >> 6) / NB;
     return wop[((((long long)f * a.S + s) * 8 + q) * a.NBT + a.c0 + c) * 64 + l];

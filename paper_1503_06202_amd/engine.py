@@ -67,7 +67,10 @@ class Plan:
     """A correlation plan for frames of N inputs, F channels, T <= T_max samples.
 
     ``form`` is "i8" (int8 MFMA, int32 accumulators) or "f8" (FP8 e4m3 MFMA,
-    f32 partial sums flushed to int32 every <= 32768 samples).  With
+    f32 partial sums flushed to int32 every <= 32768 samples) on the tile
+    kernels; both are exact, and the kernels chosen by size serve both: int8 up
+    to 256 inputs, FP6 operands (which hold every 4-bit code) and f32 sums below
+    2^24 for large frames above 640.  With
     ``accumulate`` the frame's sums are added to ``vis``.  With ``gates`` > 0
     the plan can also gate the output into up to that many buffers
     (``correlate_gated``); with ``flagged`` it can correlate frames with
