@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -661,6 +662,19 @@ static double packed_us(int N, int F, int len, bool add, int cus) {
          (add ? 0.289 * mb : 0.0) + 0.038 * sliced;
 }
 
+// The same for a frame of T samples in launches of at most seg; later ones add.
+static double frame_us(double (*us)(int, int, int, bool, int), int N, int F, int T, bool add,
+                       int seg, int cus) {
+  const int full = T / seg, rest = T % seg;
+  const double t =
+      full > 0 ? us(N, F, seg, add, cus) + (full - 1) * us(N, F, seg, true, cus) : 0.0;
+  return rest > 0 ? t + us(N, F, rest, add || full > 0, cus) : t;
+}
+
+static double packed_frame_us(int N, int F, int T, bool add, int cus) {
+  return frame_us(packed_us, N, F, T, add, XENG_F8_FLUSH_MAX, cus);
+}
+
 // When the packed path is chosen (tuning kernel 0): where its estimate is the
 // lower one, by 3% for the estimates' errors.  Packing moves 2.5 bytes of HBM
 // traffic a sample (0.52 ms for a GiB of samples) and the FP6 correlation runs
@@ -687,14 +701,8 @@ static bool packed_pays(int N, int F, int T, bool shift_copy, int form, bool add
   const long long work = tiles_per_channel(N) * F * T;
   if (shift_copy) return N >= 128 && T >= 1536 && work >= 340000;
   if (N <= 640 || T < 1024 || work < 230000) return false;
-  auto total = [&](auto&& us, int seg) {
-    const int full = T / seg, rest = T % seg;
-    double t = full > 0 ? us(seg, add) + (full - 1) * us(seg, true) : 0.0;
-    return rest > 0 ? t + us(rest, add || full > 0) : t;
-  };
-  return total([&](int len, bool a) { return packed_us(N, F, len, a, cus); }, XENG_F8_FLUSH_MAX) <
-         0.97 * total([&](int len, bool a) { return tiles_us(N, F, len, a, cus); },
-                      segment_max(form));
+  return packed_frame_us(N, F, T, add, cus) <
+         0.97 * frame_us(tiles_us, N, F, T, add, segment_max(form), cus);
 }
 
 // Workspace of a packed call: channels per group, operands and partial blocks
@@ -1390,23 +1398,95 @@ int xeng_beamform(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, in
   return mark_tables(p, s);
 }
 
-// Instances of a batch that run by the packed path, one after another, while
-// the persistent kernel takes the others.  In a batch the tiles of all frames
-// share the chip, so that a frame has to fill it alone to gain from the packed
-// path, unless all of them leave workgroups idle; microseconds, tiles (best of
-// 1, 2 and 4 slices) / packed, by 128 x 128 tiles x samples of an instance:
-//   4 x (2048, 4, 16384)  8.9 M  1579 / 1168    8 x (1024, 4, 16384)  2.4 M  854 / 949
-//   8 x (1024, 4, 32768)  4.7 M  1679 / 1631    6 x (2048, 2, 8192)   2.2 M  614 / 647
-//   2 x (1024, 4, 16384)  2.4 M   262 / 237     2 x (1024, 2, 16384)  1.2 M  183 / 142
-// A named slice count keeps the tiles.
-static bool batch_packs(const xeng_instance& d, long long batch_tiles, int form, bool add,
-                        int cus) {
-  const long long work = tiles_per_channel(d.N) * d.F * (long long)d.T;
-  return d.split_t == 0 && packed_pays(d.N, d.F, d.T, false, form, add, cus) &&
-         work >= (batch_tiles > cus * kOccupancy ? 4000000 : 1100000);
+// Estimated microseconds of the batched persistent kernel over `insts`: its work
+// items, longest first, on the slots that are free first; stores, atomic adds
+// and the clearing before them hide behind long items.  Fitted to 380 batches of 1
+// to 48 frames and 900 that packing some of their frames left (10% rms).
+static double batch_us(const std::vector<xeng_instance>& insts, int form, bool add, int cus) {
+  if (insts.empty()) return 0.0;
+  const long long slots = (long long)cus * kOccupancy;
+  long long tiles = 0;
+  for (const xeng_instance& d : insts) tiles += d.F * tiles_per_channel(d.N);
+  const int s_auto = auto_slices(tiles, XENG_T_EXACT_MAX, cus);
+  std::vector<std::pair<double, long long>> items;  // samples, how many such items
+  double us = 11.9;
+  bool cleared = false;
+  for (const xeng_instance& d : insts) {
+    int S = 0, len = 0;
+    batch_slices(d, s_auto, form, S, len);
+    items.push_back({(double)std::min(len, d.T), d.F * tiles_per_channel(d.N) * S});
+    const double mb = 4e-6 * d.F * d.N * (d.N + 1.0), shown = 500.0 / (500.0 + len);
+    us += S > 1 ? (add ? 2.09 : 4.40) * mb * S * shown
+                : (0.420 * shown + (add ? 0.174 : 0.118)) * mb;
+    cleared |= S > 1 && !add;
+  }
+  std::sort(items.rbegin(), items.rend());
+  typedef std::pair<double, long long> Load;  // samples so far, slots that have them
+  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> free;
+  free.push({0.0, slots});
+  double longest = 0.0, sum = 0.0;
+  for (auto [len, n] : items) {
+    sum += len * n;
+    while (n > 0) {
+      const Load l = free.top();
+      free.pop();
+      const long long k = std::min(n, l.second);
+      free.push({l.first + len, k});
+      longest = std::max(longest, l.first + len);
+      if (l.second > k) free.push({l.first, l.second - k});
+      n -= k;
+    }
+  }
+  return us + 0.01045 * longest + 0.0129 * sum / slots + (cleared ? 3.5 : 0.0);
 }
 
-int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, unsigned flags) {
+// Instances of a batch that run by the packed path, one after another, while
+// the persistent kernel takes the others (indices, ascending): the largest
+// ones, as many as make the estimated time of the whole call least, if that is
+// 5% below the persistent kernel's for all.  In a batch the tiles of all frames
+// share the chip, and without its largest frames the others may fill it worse;
+// microseconds, persistent kernel for all / by lines in an instance's size alone
+// (4 M tile-samples, or 1.1 M where all tiles leave slots unused) / by estimates:
+//   16 frames, N 128..2048, F = 4, T <= 8192       407 / 568 / 407
+// Of 200 batches of 1 to 48 frames (N 64..2048) 10 are more than 1% slower than
+// the persistent kernel alone for it, 2 more than 5%, and their mean is 0.833
+// times; by the lines 31, 20 and 0.947.
+// A named slice count keeps the tiles.
+static std::vector<int> batch_packed_set(const std::vector<xeng_instance>& insts, int form,
+                                         bool add, int cus) {
+  std::vector<int> large;
+  for (int k = 0; k < (int)insts.size(); ++k) {
+    const xeng_instance& d = insts[k];
+    if (d.split_t == 0 && packed_pays(d.N, d.F, d.T, false, form, add, cus)) large.push_back(k);
+  }
+  auto work = [&](int k) { return tiles_per_channel(insts[k].N) * insts[k].F * insts[k].T; };
+  std::stable_sort(large.begin(), large.end(), [&](int x, int y) { return work(x) > work(y); });
+  double best = 0.95 * batch_us(insts, form, add, cus), packed = 0.0;
+  std::vector<char> taken(insts.size(), 0);
+  size_t take = 0;
+  const size_t step = (large.size() + 31) / 32;  // at most 32 cuts
+  for (size_t m = 0; m < large.size() && packed < best; ++m) {
+    const xeng_instance& d = insts[large[m]];
+    packed += packed_frame_us(d.N, d.F, d.T, add, cus);
+    taken[large[m]] = 1;
+    if ((m + 1) % step != 0 && m + 1 < large.size()) continue;
+    std::vector<xeng_instance> others;
+    for (size_t k = 0; k < insts.size(); ++k)
+      if (!taken[k]) others.push_back(insts[k]);
+    const double t = packed + batch_us(others, form, add, cus);
+    if (t < best) {
+      best = t;
+      take = m + 1;
+    }
+  }
+  large.resize(take);
+  std::sort(large.begin(), large.end());
+  return large;
+}
+
+// pack: some instances may run by the packed path
+static int plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, unsigned flags,
+                      bool pack) {
   if (!out) return XENG_EINVAL;
   *out = nullptr;
   if (!descs || count < 1 || !flags_ok(flags, true)) return XENG_EINVAL;
@@ -1479,20 +1559,18 @@ int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, uns
     delete p;
     return XENG_EINVAL;
   }
-  if (!shared) {
+  if (pack && !shared) {  // (a vis shared between instances takes atomic adds: tiles)
     try {
-      // a vis shared between instances takes atomic adds: tiles
+      p->large = batch_packed_set(p->insts, p->form, p->accumulate, cu_count_hint());
       std::vector<xeng_instance> others;
-      long long tiles = 0;
-      for (int k = 0; k < count; ++k) tiles += descs[k].F * tiles_per_channel(descs[k].N);
-      for (int k = 0; k < count; ++k) {
-        if (batch_packs(descs[k], tiles, p->form, p->accumulate, cu_count_hint()))
-          p->large.push_back(k);
+      for (int k = 0, l = 0; k < count; ++k) {
+        if (l < (int)p->large.size() && p->large[l] == k)
+          ++l;
         else
           others.push_back(descs[k]);
       }
       if (!p->large.empty() && !others.empty()) {
-        const int rc = xeng_plan_batch(&p->rest, others.data(), (int)others.size(), flags);
+        const int rc = plan_batch(&p->rest, others.data(), (int)others.size(), flags, false);
         if (rc != XENG_OK) {
           xeng_destroy(p);
           return rc;
@@ -1505,6 +1583,10 @@ int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, uns
   }
   *out = p;
   return XENG_OK;
+}
+
+int xeng_plan_batch(xeng_plan_t* out, const xeng_instance* descs, int count, unsigned flags) {
+  return plan_batch(out, descs, count, flags, true);
 }
 
 static int batch_setup(xeng_plan_t p) {

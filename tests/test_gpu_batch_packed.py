@@ -54,8 +54,19 @@ def test_batch_with_large_frames(insts, form, accumulate):
 
 
 
+# batches of few tiles whose largest frame, or all frames, run packed
+FEW_PACKED = [(64, 2, 300), (1536, 2, 20000), (1090, 1, 33000), (17, 1, 5)]
+
+
+@pytest.mark.parametrize("insts", [FEW_PACKED, [(2048, 2, 16384), (64, 3, 1000), (1090, 2, 20000)],
+                                   [(1537, 4, 13001)]])
+@pytest.mark.parametrize("form,accumulate", [("i8", False), ("f8", True)])
+def test_batch_of_few_tiles(insts, form, accumulate):
+    test_batch_with_large_frames(insts, form, accumulate)
+
+
 @pytest.mark.parametrize("graph", [False, True])
-@pytest.mark.parametrize("insts", [FEW, MANY])
+@pytest.mark.parametrize("insts", [FEW_PACKED, MANY])
 def test_captured_after_a_call_by_the_packed_path(insts, graph):
     # a program's usual order: one call, then the same call captured; other
     # eager calls (the same buffers) between the replays

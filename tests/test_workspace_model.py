@@ -1,6 +1,7 @@
 """A plan's workspace on a model of the HIP runtime (workspace_model.cpp): the
 C ABI's host code, compiled as it is, with streams that race, handles that are
-given out again, captures and memory that is refused."""
+given out again, captures and memory that is refused; and the paths it chooses
+for frames and batches that were measured on each."""
 import os
 import subprocess
 
@@ -24,7 +25,7 @@ def model(tmp_path_factory):
 
 @pytest.mark.parametrize("shape", [0, 1, 2], ids=["small", "channel", "packed"])
 @pytest.mark.parametrize("scenario", ["streams_in_turn", "per_thread", "reused_handles", "growth",
-                                      "refused", "captured", "two_devices", "last_segment", "bounded_slices", "one_shot", "paths"])
+                                      "refused", "captured", "two_devices", "last_segment", "bounded_slices", "one_shot", "paths", "batches"])
 def test_workspace(model, scenario, shape):
     res = subprocess.run([model, scenario, str(shape)], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0 and res.stdout == "ok\n", res.stdout + res.stderr

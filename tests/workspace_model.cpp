@@ -326,6 +326,31 @@ void paths(Shape) {
     check((tiles > 0) == c.tiles, "the slower path");
   }
 }
+void batches(Shape) {
+  // the frames of a batch that run packed
+  auto packs = [](std::vector<xeng_instance> b, unsigned flags = 0) {
+    xeng_plan_t p = nullptr;
+    check(xeng_plan_batch(&p, b.data(), (int)b.size(), flags) == XENG_OK, "batch plan");
+    check(!p->rest || p->rest->large.empty(), "the others' own plan packs none");
+    check(p->large.empty() || p->large.size() == b.size() || p->rest, "a plan of the others");
+    return p->large;
+  };
+  typedef std::vector<int> L;
+  check(packs({{2048, 4, 8192, 0}, {300, 2, 1000, 0}, {1537, 4, 13001, 0}, {128, 3, 129, 0}}) ==
+            L{0, 2}, "large frames among small ones");
+  check(packs({{64, 2, 300, 0}, {1536, 2, 20000, 0}, {1090, 1, 33000, 0}, {17, 1, 5, 0}}) == L{1},
+        "few tiles");
+  check(packs({{1537, 4, 13001, 0}}) == L{0}, "all of them");
+  check(packs({{1537, 4, 13001, 2}}).empty(), "a named slice count");
+  check(packs({{1537, 4, 13001, 0}}, XENG_ACCUMULATE | XENG_SHARED_VIS).empty(), "shared vis");
+  // measured: 407 us by the persistent kernel alone, 568 with the first frame packed
+  std::vector<xeng_instance> mixed = {{2048, 4, 8192, 0}, {2048, 4, 4096, 0}};
+  for (int T : {2048, 2048}) mixed.push_back({1024, 4, T, 0});
+  for (int T : {8192, 8192, 8192, 2048, 2048, 2048, 2048, 2048}) mixed.push_back({512, 4, T, 0});
+  for (int N : {256, 128})
+    for (int T : {8192, 4096}) mixed.push_back({N, 4, T, 0});
+  check(packs(mixed).empty(), "frames that fill the chip together");
+}
 void one_shot(Shape) {
   // a plan that serves one call: no workspace that the call does not gain back
   struct { Shape s; bool workspace; } const calls[] = {
@@ -348,7 +373,8 @@ int main(int argc, char** argv) {
       {"refused", refused},                 {"captured", captured},
       {"two_devices", two_devices},         {"last_segment", last_segment},
       {"bounded_slices", bounded_slices},
-      {"one_shot", one_shot},               {"paths", paths}};
+      {"one_shot", one_shot},               {"paths", paths},
+      {"batches", batches}};
   if (argc != 3 || !all.count(argv[1])) return 2;
   all.at(argv[1])(kShapes[std::atoi(argv[2])]);
   std::printf("ok\n");
