@@ -691,18 +691,28 @@ static double packed_frame_us(int N, int F, int T, bool add, int cus) {
 // the tiles' last wave leaves a tenth of the slots unused) had 130 of 1300, up to
 // 1.55 times.  Below 230,000 tile-samples (128 x 128 tiles x samples) the
 // estimates are not close enough.
-// Delays that differ inside a block of 128 inputs (shift_copy) cost the tile
-// kernels a copy of the frame that fetches every line eight times (1.39 ms a
-// GiB), and the packed path only a longer packing pass (0.93 ms): there it
-// pays from 128 inputs on,
+// Delays that differ inside a block of 128 inputs (dmax, the largest; else -1)
+// cost the tile kernels a copy of the frame that fetches every line eight times
+// (1.39 ms for a GiB of 2048 inputs), and the packed path only a longer packing
+// pass (0.93 ms): there it pays from 128 inputs on,
 //   N = 128, F = 16, T = 32768  131 / 110    N = 384, F = 64, T = 4096   259 / 130
 //   N = 512, F = 4,  T = 8192 (328,000)  80 / 64    N = 512, F = 1, T = 32768 (328,000)  76 / 81
-static bool packed_pays(int N, int F, int T, bool shift_copy, int form, bool add, int cus) {
+// from 340,000 tile-samples and 1536 samples, where its estimate is the lower one
+// (N = 224, F = 57, T = 2043, D = 13737, accumulated 78 / 103; N = 144, F = 6, T =
+// 28605 69 / 83).  The estimates fit 274 frames of 128..2048 inputs (packed 5%,
+// tiles 7% rms; the copy costs three times as much where rows are not aligned): 2
+// of them are more than 1% slower for it, 10 by the sizes alone.
+static bool packed_pays(int N, int F, int T, int dmax, int form, bool add, int cus) {
   const long long work = tiles_per_channel(N) * F * T;
-  if (shift_copy) return N >= 128 && T >= 1536 && work >= 340000;
-  if (N <= 640 || T < 1024 || work < 230000) return false;
-  return packed_frame_us(N, F, T, add, cus) <
-         0.97 * frame_us(tiles_us, N, F, T, add, segment_max(form), cus);
+  if (dmax < 0 ? N <= 640 || T < 1024 || work < 230000 : N < 128 || T < 1536 || work < 340000)
+    return false;
+  const double packed = packed_frame_us(N, F, T, add, cus);
+  const double tiles = frame_us(tiles_us, N, F, T, add, segment_max(form), cus);
+  if (dmax < 0) return packed < 0.97 * tiles;
+  const double mb = 1e-6 * N * F * T;  // samples, and those that packing reads
+  const double read = 1e-6 * ((N + kTile - 1) / kTile * kTile) * F * ((double)T + dmax);
+  const double copy = 0.78 + (N % 16 != 0 ? 1.64 : 0.0) + (dmax > 2000 ? 0.25 : 0.0);
+  return 8.7 + 0.070 * mb + 0.136 * read + 0.93 * packed < 2.9 + copy * mb + 1.05 * tiles;
 }
 
 // Workspace of a packed call: channels per group, operands and partial blocks
@@ -801,7 +811,7 @@ static int launch_packed_path(xeng_plan_t p, const PackedNeed& need, const uint8
 // Whether an automatic plan takes such a frame by the packed path (for the
 // benchmark's labels; not part of the C ABI in include/xeng.h).
 int xeng_takes_packed(int N, int F, int T, int form) {
-  return packed_pays(N, F, T, false, form, false, cu_count_hint());
+  return packed_pays(N, F, T, -1, form, false, cu_count_hint());
 }
 
 // A plan that serves one call (the Python face's one-shot correlation; not part
@@ -907,7 +917,8 @@ int xeng_correlate(xeng_plan_t p, const uint8_t* samples, int N, int F, int T, i
   int rc = ensure_cu_count(p);
   if (rc != XENG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->kernel == 0 && packed_pays(N, F, T, p->shift && p->shift_copy, p->form, p->accumulate, p->cu_count) &&
+  if (p->kernel == 0 && packed_pays(N, F, T, p->shift && p->shift_copy ? p->shift_max : -1, p->form,
+                                    p->accumulate, p->cu_count) &&
       !stream_captures(s)) {
     rc = correlate_packed(p, samples, N, F, T, vis, s);
     if (rc != XENG_ENOMEM) return rc;
@@ -1457,7 +1468,7 @@ static std::vector<int> batch_packed_set(const std::vector<xeng_instance>& insts
   std::vector<int> large;
   for (int k = 0; k < (int)insts.size(); ++k) {
     const xeng_instance& d = insts[k];
-    if (d.split_t == 0 && packed_pays(d.N, d.F, d.T, false, form, add, cus)) large.push_back(k);
+    if (d.split_t == 0 && packed_pays(d.N, d.F, d.T, -1, form, add, cus)) large.push_back(k);
   }
   auto work = [&](int k) { return tiles_per_channel(insts[k].N) * insts[k].F * insts[k].T; };
   std::stable_sort(large.begin(), large.end(), [&](int x, int y) { return work(x) > work(y); });

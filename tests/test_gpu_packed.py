@@ -197,3 +197,10 @@ def test_packed_segments_and_short_frames(N, T, F, form):
     s = rand_frame(N + T, T, F, N)
     print(f"packed N={N} F={F} T={T} form={form}", flush=True)
     assert np.array_equal(gpu(s, form), want(s))
+
+
+@pytest.mark.parametrize("N,F,T,D", [(144, 60, 6011, 31), (650, 2, 33000, 20000),
+                                     (1040, 1, 33000, 300), (704, 3, 5600, 300), (768, 2, 5600, 300)])
+def test_packed_group_delays_in_odd_blocks_and_segments(N, F, T, D):
+    print(f"group delays N={N} F={F} T={T} D={D}", flush=True)
+    test_packed_group_delays(N, F, T, D)
