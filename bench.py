@@ -105,6 +105,15 @@ def _time_calls(fn, steps, torch, warm_s=0.3):
     return (time.perf_counter() - t0) * 1e3 / steps
 
 
+def mfma_operands(w, form):
+    """What the matrix cores multiply on this frame: FP6 on the packed path (both
+    forms; the 4-bit codes are FP6 numbers as they stand), else the form's own."""
+    from paper_1503_06202_amd import _lib
+    from paper_1503_06202_amd.engine import FORMS
+
+    return "f6" if _lib.lib().xeng_takes_packed(w.N, w.F, w.T, FORMS[form]) else form
+
+
 def bench_fp8(d, w, steps, torch):
     """The FP8 e4m3 form on the same frame (f32 sums flushed to int32)."""
     from paper_1503_06202_amd import Plan, vis_shape
@@ -114,14 +123,16 @@ def bench_fp8(d, w, steps, torch):
         ms = _time_calls(lambda: p.correlate(d, vis), steps, torch)
     ops = 8.0 * w.cmac / (ms / 1e3) / 1e12
     return {"workload": w.name, "ms_per_frame": ms, "cmac_per_s": w.cmac / (ms / 1e3),
-            "tflops": ops, "pct_fp8_peak": 100.0 * ops / PEAK_TOPS["f8"]}
+            "tflops": ops, "mfma_operands": mfma_operands(w, "f8"),
+            "pct_mfma_peak": 100.0 * ops / PEAK_TOPS[mfma_operands(w, "f8")],
+            "pct_fp8_peak": 100.0 * ops / PEAK_TOPS["f8"]}
 
 
 def bench_precision(steps, torch):
     """FP8 beside int8 on the precision workload (N = 2048, F = 16,
-    T = 131072; 4 GiB per frame).  The FP8 form flushes its f32 sums to int32
-    every 32768 samples, i.e. four launches per frame; int8 takes the frame in
-    one launch."""
+    T = 131072; 4 GiB per frame).  Both forms take the packed path, which adds
+    its f32 sums into the int32 output every 32768 samples, i.e. four times per
+    frame."""
     import synth
     from paper_1503_06202_amd import Plan
 
@@ -138,6 +149,8 @@ def bench_precision(steps, torch):
             ms = _time_calls(lambda: p.correlate(d, vis), max(4, steps // 2), torch)
         ops = 8.0 * w.cmac / (ms / 1e3) / 1e12
         out[form] = {"ms_per_frame": ms, "cmac_per_s": w.cmac / (ms / 1e3), "tflops": ops,
+                     "mfma_operands": mfma_operands(w, form),
+                     "pct_mfma_peak": 100.0 * ops / PEAK_TOPS[mfma_operands(w, form)],
                      "pct_peak": 100.0 * ops / PEAK_TOPS[form]}
     del d, vis
     return out
@@ -537,7 +550,7 @@ def main():
     import torch
 
     import synth
-    from paper_1503_06202_amd import Plan, _lib, vis_shape
+    from paper_1503_06202_amd import Plan, vis_shape
 
     if not torch.cuda.is_available():
         print("bench.py needs a GPU", file=sys.stderr)
@@ -577,10 +590,9 @@ def main():
     value = cmac / (ms_step / 1e3)
     ops_per_launch = 8.0 * cmac          # 1 complex MAC = 4 real MACs = 8 ops
     achieved = ops_per_launch / (ev_avg / 1e3) / 1e12
-    # large frames of more than 640 inputs run on FP6 operands (both forms; the
-    # 4-bit codes are FP6 numbers as they stand): priced against the FP6 peak
-    packed = bool(_lib.lib().xeng_takes_packed(w.N, w.F, w.T, {"i8": 0, "f8": 1}[args.form]))
-    peak = PEAK_TOPS["f6" if packed else args.form]
+    operands = mfma_operands(w, args.form)
+    packed = operands == "f6"
+    peak = PEAK_TOPS[operands]
     frame_s = w.T * SAMPLE_PERIOD_S
     channels_rt = w.F * frame_s / (ms_step / 1e3)
 

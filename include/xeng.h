@@ -119,8 +119,8 @@ int xeng_plan(xeng_plan_t *out, int N, int F, int T_max, unsigned flags);
  * S grows).  A named split_t whose partial outputs, here or on the packed path,
  * would pass 1 GiB takes the tile kernels, unless the plan names the channel
  * kernel.
- * Frames of more than 640 inputs and enough work take the packed path (unless
- * the plan names a kernel): the samples are repacked into FP6 operands (the
+ * Frames of more than 640 inputs take the packed path where its estimated time is
+ * the lower one (unless the plan names a kernel): the samples are repacked into FP6 operands (the
  * 4-bit codes are FP6 numbers as they stand) and correlated on FP6 matrix
  * cores, exactly, in segments of at most XENG_F8_FLUSH_MAX samples.  The
  * operands (1.5 bytes a sample of one segment) and the partial outputs of
@@ -162,10 +162,10 @@ int xeng_correlate(xeng_plan_t p, const uint8_t *samples, int N, int F, int T,
  *            through the loads and N > 256 use 1).  Automatic, both forms: the
  *            small-array kernel at N <= 128 (whole channels of 16, 32, 64 or
  *            128 columns per workgroup), the channel kernel at 128 < N <= 256
- *            (F N <= 2^25), both without shifting in the loads; the packed
- *            path (see xeng_correlate) on large frames of more than 640 inputs;
- *            else 1,
- *            the fastest on gfx950 at the measured sizes; the autotuner
+ *            (F N <= 2^25; in the FP8 form where it is faster by an estimate),
+ *            both without shifting in the loads; the packed path (see
+ *            xeng_correlate) above 640 inputs where it is faster by an estimate;
+ *            else 1.  The autotuner
  *            (tune.tune_plain) picks per shape.
  * Errors: XENG_EINVAL (NULL plan, negative split_t, kernel outside 0..5).
  */

@@ -2,9 +2,9 @@
 // FP6 MFMA, operands as xeng_pack.hip laid them out (xeng_packed.hpp).
 //
 // A 4-bit code is an FP6 e2m3 number as it stands, and the FP6 matrix cores
-// run twice the rate of the int8 and FP8 ones: MFMA-only code reaches 7.35
-// POP/s on codes (1.8 GHz, at the power limit) against 3.58 in int8 and 4.93
-// in FP8.  The sums of products of codes are integers below 450 T < 2^24 over
+// run twice the rate of the int8 and FP8 ones: MFMA-only code reaches 7.35 to
+// 7.55 POP/s on codes (1.85 GHz, at the power limit; mfma_ceiling.hip) against
+// 3.53 to 3.64 in int8 and 4.93 in FP8.  The sums of products of codes are integers below 450 T < 2^24 over
 // one segment (T <= XENG_F8_FLUSH_MAX), exact in f32 in any order.
 //
 // What bounds it is power: on 2048 inputs, 16 channels, 32768 samples it takes
