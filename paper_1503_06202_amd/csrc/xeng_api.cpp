@@ -441,9 +441,9 @@ static int workspace_record(xeng_plan_t p, hipStream_t s) {
 // (after the plan's last call that used it), and ordered after that call.
 // Every use records an event that the next one waits for on its stream, except
 // while all uses are on the null stream, which orders them itself and is never
-// destroyed: an event costs more than a small frame (12.2 us a call with, 7.4
-// without, 16 inputs and 256 samples in two slices).  The first use on another
-// stream records the event for those before it.  An equal handle says nothing
+// destroyed: an event is a good part of a small frame's call (N = 64, F = 4, T =
+// 8192: 14.8 us with, 12.0 without).  The first use on another stream records
+// the event for those before it.  An equal handle says nothing
 // on other streams: hipStreamPerThread is another one in every thread, and the
 // handles of destroyed streams are given out again.
 // XENG_ENOMEM: the call has to do without (no memory, a stream of another device

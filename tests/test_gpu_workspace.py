@@ -101,18 +101,20 @@ def test_first_and_growing_calls_beside_a_capture(N, F, T):
     x, ref = frames(N, F, T, 1)
     half = x[0][:T // 2]
     ref_half = oracle.to_int32(oracle.correlate(half.cpu().numpy()))
-    vis = [torch.zeros(vis_shape(N, F), dtype=torch.int32, device=DEV) for _ in range(3)]
+    vis = [torch.zeros(vis_shape(N, F), dtype=torch.int32, device=DEV) for _ in range(5)]
     a, b, other = torch.ones(64, device=DEV), torch.zeros(64, device=DEV), torch.cuda.Stream()
     torch.cuda.synchronize()
     print(f"beside a capture N={N} F={F} T={T}", flush=True)
-    with Plan(N, F, T) as p, Plan(N, F, T) as q:
+    with Plan(N, F, T) as p, Plan(N, F, T) as q, Plan(N, F, T) as r:
         q.correlate(half, vis[2], stream=other)  # its workspace grows below
+        r.correlate(half, vis[3])  # on the null stream, then beside the capture
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             b.add_(a)
             p.correlate(x[0], vis[0], stream=other)
             q.correlate(x[0], vis[1], stream=other)
+            r.correlate(x[0], vis[4], stream=other)
         for k in range(1, 4):
             g.replay()
             torch.cuda.synchronize()
@@ -120,3 +122,5 @@ def test_first_and_growing_calls_beside_a_capture(N, F, T):
     assert np.array_equal(vis[0].cpu().numpy(), ref[0])
     assert np.array_equal(vis[1].cpu().numpy(), ref[0])
     assert np.array_equal(vis[2].cpu().numpy(), ref_half)
+    assert np.array_equal(vis[3].cpu().numpy(), ref_half)
+    assert np.array_equal(vis[4].cpu().numpy(), ref[0])
